@@ -81,11 +81,12 @@ enum pot3d_iteration {
     POT3D_ITER_ONE_SWEEP = 1   /* one sweep per iteration: the r/x update of iteration j-1
                                   and the direction update of iteration j together, with
                                   r.z of the next residual predicted from p.Ap, z.Ap and
-                                  Ap.D^-1 Ap.  x is updated once per pair of sweeps, the
-                                  earlier increment rebuilt from p and z: 40 bytes per
-                                  unknown per iteration in FP64, 20 in FP32 (48 and 24
-                                  with POT3D_SWEEP_X=1 in the environment, x every sweep).
-                                  The same PCG in exact arithmetic.  Default.               */
+                                  Ap.D^-1 Ap.  The residual is rebuilt from the last two
+                                  directions, and x is updated once per pair of sweeps
+                                  from them: 32 bytes per unknown per iteration in FP64,
+                                  16 in FP32 (40 and 20 with POT3D_SWEEP_X=1 in the
+                                  environment, x every sweep).  The same PCG in exact
+                                  arithmetic.  Default.                                  */
 };
 
 enum pot3d_preconditioner {
@@ -115,11 +116,13 @@ typedef struct pot3d_stats {
     double relres_true;      /* ||b - A Phi||/||b||, recomputed in FP64 at exit             */
     double solve_ms;         /* wall time of the last solve call on the device             */
     double loop_ms;          /* device time of the iteration loop (hipEvents)               */
-    double bytes_per_iter;   /* algorithmic HBM bytes of one iteration, x once per pair of
+    double bytes_per_iter;   /* reference HBM bytes of one iteration: every vector of the
+                                recurrence (r, p, and z with the phi-line preconditioner)
+                                read and written where a pass needs it, x once per pair of
                                 iterations (with POT3D_SWEEP_X=1, x every iteration): FP64
                                 40 N (48 N) one sweep, 60 N (64 N) two passes, 76 N (80 N)
                                 with the phi-line preconditioner; FP32 inner iterations
-                                half of each                                               */
+                                half of each.  The kernels may move fewer (see above)      */
     long long n;             /* unknowns nr*nt*np                                            */
     int pitch;               /* row pitch (elements) of the internal phi-fastest arrays    */
     int tile_p, tile_r;      /* stencil kernel shape of the p update and of the r/x update:

@@ -460,9 +460,10 @@ int sweep_xmode(int it)
     return (it & 1) ? 2 : 1;
 }
 
-// HBM bytes per unknown per iteration of the one-sweep form: read r, p_old
-// and write r, p in every sweep, read and write x in every other one
-// (every one with POT3D_SWEEP_X=1).
+// Bytes per unknown per iteration that pot3d_stats reports for the one-sweep
+// form: r and p read and written in every iteration, x in every other one
+// (every one with POT3D_SWEEP_X=1).  The kernels move 8 (FP32: 4) fewer,
+// since they carry the last two directions instead of r and p.
 double sweep_bytes(bool fp32)
 {
     const double b = env_int("POT3D_SWEEP_X", 2) == 1 ? 48.0 : 40.0;
@@ -486,26 +487,17 @@ double two_pass_bytes(bool fp32, int m)
 }
 
 // Capture 2 m sweeps of the one-sweep iteration (sweep, finisher) on the
-// idle context stream.  Sweep j reads r and p from buffer j mod 2 and writes
-// buffer (j + 1) mod 2; 2 m is even, so replays continue the alternation,
-// and of the x pairing too (an even sweep leaves x to the odd one after it).
+// idle context stream.  The sweeps take their place in the ring of three
+// direction buffers from the device's sweep count; 2 m is even, so replays
+// continue the x pairing (an even sweep leaves x to the odd one after it).
 template <typename V>
-int capture_sweeps(pot3d_ctx *c, V *r0, V *r1, V *p0, V *p1, V *x, DevScalars *sc, hipGraphExec_t *out)
+int capture_sweeps(pot3d_ctx *c, V *r, V *p0, V *p1, V *x, DevScalars *sc, hipGraphExec_t *out)
 {
     hipStream_t s = c->stream;
     HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    V *rb[2] = {r0, r1};
-    V *pb[2] = {p0, p1};
     for (int it = 0; it < 2 * c->graph_m && e == hipSuccess; ++it) {
-        SweepVecs<V> v{};
-        v.r_in = rb[it & 1];
-        v.r_out = rb[(it + 1) & 1];
-        v.p_old = pb[it & 1];
-        v.p_new = pb[(it + 1) & 1];
-        v.x = x;
-        v.sc = sc;
-        v.partial = c->partial;
+        SweepVecs<V> v = sweep_vecs<V>(r, p0, p1, x, sc, c->partial);
         v.xmode = sweep_xmode(it);
         e = launch_sweep<V>(c->sweep_rows, c->grid_s, v, s);
         if (e == hipSuccess) e = launch_finish(kFinSweep, sc, c->partial, c->grid_s.nblocks, s);
@@ -615,9 +607,9 @@ void free_ctx(pot3d_ctx *c)
     for (hipEvent_t *e : {&c->ev_poll[0], &c->ev_poll[1], &c->ev_t0, &c->ev_t1, &c->ev_loop0, &c->ev_loop1})
         if (*e) (void)hipEventDestroy(*e);
     if (c->stream) (void)hipStreamDestroy(c->stream);
-    void *bufs[] = {c->rows, c->dphi, c->ih, c->bfac, c->x, c->r, c->r2, c->p[0], c->p[1],
+    void *bufs[] = {c->rows, c->dphi, c->ih, c->bfac, c->x, c->r, c->p[0], c->p[1],
                     c->bplane, c->br, c->partial, c->poles, c->vr, c->vt, c->bcs, c->ftab, c->sc,
-                    c->r32, c->r32b, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32};
+                    c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (c->h_sc) (void)hipHostFree(c->h_sc);
@@ -671,7 +663,9 @@ int prepare_solve(pot3d_ctx *c, const double *br_dev, const double *phi0, hipMem
 }
 
 // FP64 start: scalars, p_old = 0, r = b - A x0 and the first residual test.
-int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit)
+// sweeps: the one-sweep iteration follows, which starts from z = D^-1 r
+// (stored in r's place).
+int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit, bool sweeps)
 {
     DevScalars init{};
     init.tol = tol;
@@ -683,7 +677,7 @@ int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit)
     rv.in = c->x;
     rv.r = c->r;
     rv.bplane = c->bplane;
-    rv.store_r = 1;
+    rv.store_r = sweeps ? 2 : 1;
     rv.ignore_done = 1;
     HIP_TRY(c, launch_stencil<double>(kResidual, c->tile_o, c->grid_o, rv, s));
     HIP_TRY(c, launch_finish(kFinInit, c->sc, c->partial, c->grid_o.nblocks, s));
@@ -701,13 +695,13 @@ int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit)
 int run_fp64(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream_t s, double tol, int maxit, int *iters,
              double *relres_true)
 {
-    int rc = start_fp64(c, s, tol, maxit);
+    const bool line = c->precond == POT3D_PC_PHI_LINE;
+    const bool sweep = !line && one_sweep(c);
+    int rc = start_fp64(c, s, tol, maxit, sweep);
     if (rc != POT3D_OK) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_loop0, s));
     int launches = 0;
     DevScalars fin{};
-    const bool line = c->precond == POT3D_PC_PHI_LINE;
-    const bool sweep = !line && one_sweep(c);
     hipGraphExec_t graph = line ? c->graph_l : (sweep ? c->graph_s : c->graph);
     rc = replay_until_done(c, graph, c->sc, s, maxit, sweep ? 2 * c->graph_m : c->graph_m, &launches, &fin);
     if (rc != POT3D_OK) return rc;
@@ -757,8 +751,10 @@ double inner_tolerance(const pot3d_ctx *c)
     return c->refine_mode == POT3D_REFINE_RELIABLE ? 0.1 : 1e-4;
 }
 
+// sweeps: the segments run in the one-sweep form, which starts from z = D^-1 r
+// and leaves its last direction in another buffer than the two-pass form.
 int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left, const DevScalars &outer,
-                        const DevScalars *prev, double scale_prev)
+                        const DevScalars *prev, double scale_prev, bool sweeps)
 {
     const int nb_dots = std::max(1, std::min(c->max_blocks, c->nr * c->nt));
     const bool resume = c->refine_mode == POT3D_REFINE_RELIABLE && prev && prev->done && prev->status == POT3D_OK &&
@@ -774,8 +770,9 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
         // a capped segment (status ENOCONV) makes the next one a restart.
         in.maxit = (int)std::min<long long>(maxit_left, 2LL * prev->k + 64);
         const double f = outer.scale / scale_prev;   // new units per old unit
-        HIP_TRY(c, launch_resume_residual(c->r, c->r32, c->e32, c->p32[prev->k & 1], c->p32[0], c->npad, c->sc,
-                                          (float)f, s));
+        const SweepVecs<float> sv = sweep_vecs<float>(c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->partial);
+        const float *last = sweeps ? sv.ring[(prev->k + 2) % 3] : c->p32[prev->k & 1];
+        HIP_TRY(c, launch_resume_residual(c->r, c->r32, c->e32, last, c->p32[0], c->npad, c->sc, (float)f, s));
         in.scale = 1.0 / (f * f * prev->rho);   // 1 / rho_prev in the new units
     } else {
         HIP_TRY(c, launch_cast_residual(c->r, c->r32, c->e32, c->p32[0], c->npad, c->sc, s));
@@ -788,7 +785,7 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
         HIP_TRY(c, launch_finish(resume ? kFinResume : kFinInner, c->sc32, c->partial, c->line_blocks, s));
         return POT3D_OK;
     }
-    HIP_TRY(c, launch_dots_rz(c->grid_o, c->r32, c->partial, nb_dots, s));
+    HIP_TRY(c, launch_dots_rz(c->grid_o, c->r32, c->partial, nb_dots, sweeps, s));
     HIP_TRY(c, launch_finish(resume ? kFinResume : kFinInner, c->sc32, c->partial, nb_dots, s));
     return POT3D_OK;
 }
@@ -824,11 +821,11 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
             out.status = POT3D_ENOCONV;
             break;
         }
-        rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev);
-        if (rc != POT3D_OK) return rc;
-        scale_prev = out.scale;
         const bool line = c->precond == POT3D_PC_PHI_LINE;
         const bool sweep = !line && one_sweep(c);
+        rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev, sweep);
+        if (rc != POT3D_OK) return rc;
+        scale_prev = out.scale;
         rc = replay_until_done(c, line ? c->graph32l : (sweep ? c->graph32s : c->graph32), c->sc32, s, maxit - total,
                                sweep ? 2 * c->graph_m : c->graph_m, &launches, &inner);
         if (rc != POT3D_OK) return rc;
@@ -940,7 +937,7 @@ int time_pair(pot3d_ctx *ctx, V *r, V *p0, V *p1, V *x, DevScalars *sc, int reps
     if constexpr (std::is_same<V, double>::value) {
         // a real fixed-count PCG from x = 0 on the context's right-hand side
         HIP_TRY(ctx, launch_fill<double>(ctx->x, ctx->npad, 0.0, s));
-        const int rc = start_fp64(ctx, s, 0.0, 1 << 30);
+        const int rc = start_fp64(ctx, s, 0.0, 1 << 30, false);
         if (rc != POT3D_OK) return rc;
     } else {
         DevScalars st{};
@@ -1027,14 +1024,13 @@ int time_pair(pot3d_ctx *ctx, V *r, V *p0, V *p1, V *x, DevScalars *sc, int reps
 // FP64 PCG from x = 0 on the context's right-hand side.  ms_even, ms_odd: the
 // even sweeps (x left to the next sweep) and the odd ones (x of the pair).
 template <typename V>
-int time_sweeps(pot3d_ctx *ctx, V *r0, V *r1, V *p0, V *p1, V *x, DevScalars *sc, int reps, double *ms_even,
-                double *ms_odd)
+int time_sweeps(pot3d_ctx *ctx, V *r, V *p0, V *p1, V *x, DevScalars *sc, int reps, double *ms_even, double *ms_odd)
 {
     hipStream_t s = ctx->stream;
-    const int m = std::max(2, reps + (reps & 1));   // even: the buffers alternate across the two replays
+    const int m = std::max(2, reps + (reps & 1));   // even: the x pairing continues across the two replays
     if constexpr (std::is_same<V, double>::value) {
         HIP_TRY(ctx, launch_fill<double>(ctx->x, ctx->npad, 0.0, s));
-        const int rc = start_fp64(ctx, s, 0.0, 1 << 30);
+        const int rc = start_fp64(ctx, s, 0.0, 1 << 30, true);
         if (rc != POT3D_OK) return rc;
     } else {
         // fixed scalars on whatever the FP32 vectors hold
@@ -1056,19 +1052,10 @@ int time_sweeps(pot3d_ctx *ctx, V *r0, V *r1, V *p0, V *p1, V *x, DevScalars *sc
     }
     unsigned long long *d_ts = nullptr;
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void **>(&d_ts), init.size() * sizeof(unsigned long long)));
-    V *rb[2] = {r0, r1};
-    V *pb[2] = {p0, p1};
     hipGraphExec_t exec = nullptr;
     hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     for (int it = 0; it < m && e == hipSuccess; ++it) {
-        SweepVecs<V> v{};
-        v.r_in = rb[it & 1];
-        v.r_out = rb[(it + 1) & 1];
-        v.p_old = pb[it & 1];
-        v.p_new = pb[(it + 1) & 1];
-        v.x = x;
-        v.sc = sc;
-        v.partial = ctx->partial;
+        SweepVecs<V> v = sweep_vecs<V>(r, p0, p1, x, sc, ctx->partial);
         v.ignore_done = 1;
         v.tstamp = d_ts + 2 * it;
         v.xmode = sweep_xmode(it);
@@ -1203,10 +1190,6 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     CREATE_TRY(launch_fill<double>(c->bplane, (long long)nt * c->pitch, 0.0, c->stream));
     CREATE_TRY(launch_fill<double>(c->poles, 2LL * nr, 0.0, c->stream));
     CREATE_TRY(hipMemsetAsync(c->sc, 0, sizeof(DevScalars), c->stream));
-    if (sweep_capable(c) && precision == POT3D_FP64) {
-        CREATE_TRY(dalloc(&c->r2, (size_t)c->npad));
-        CREATE_TRY(launch_fill<double>(c->r2, c->npad, 0.0, c->stream));
-    }
     CREATE_TRY(hipStreamSynchronize(c->stream));
     set_tables(c);
     if (precision == POT3D_FP32_REFINED) {
@@ -1215,9 +1198,8 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
         CREATE_TRY(dalloc(&c->p32[1], (size_t)c->npad));
         CREATE_TRY(dalloc(&c->e32, (size_t)c->npad));
         CREATE_TRY(dalloc(&c->sc32, 1));
-        if (sweep_capable(c)) CREATE_TRY(dalloc(&c->r32b, (size_t)c->npad));
-        for (float *b : {c->r32, c->r32b, c->p32[0], c->p32[1], c->e32})
-            if (b) CREATE_TRY(launch_fill<float>(b, c->npad, 0.0f, c->stream));
+        for (float *b : {c->r32, c->p32[0], c->p32[1], c->e32})
+            CREATE_TRY(launch_fill<float>(b, c->npad, 0.0f, c->stream));
         CREATE_TRY(hipMemsetAsync(c->sc32, 0, sizeof(DevScalars), c->stream));
         CREATE_TRY(hipStreamSynchronize(c->stream));
     }
@@ -1225,10 +1207,10 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     // The iteration graphs are captured once, on the idle context stream
     // (serving slots iterate inside the server's batched graph instead).
     int gc = serving ? POT3D_OK : capture_iterations<double>(c, c->r, c->p[0], c->p[1], c->x, c->sc, &c->graph);
-    if (gc == POT3D_OK && c->r2 && !serving)
-        gc = capture_sweeps<double>(c, c->r, c->r2, c->p[0], c->p[1], c->x, c->sc, &c->graph_s);
-    if (gc == POT3D_OK && c->r32b && !serving)
-        gc = capture_sweeps<float>(c, c->r32, c->r32b, c->p32[0], c->p32[1], c->e32, c->sc32, &c->graph32s);
+    if (gc == POT3D_OK && sweep_capable(c) && precision == POT3D_FP64 && !serving)
+        gc = capture_sweeps<double>(c, c->r, c->p[0], c->p[1], c->x, c->sc, &c->graph_s);
+    if (gc == POT3D_OK && sweep_capable(c) && precision == POT3D_FP32_REFINED && !serving)
+        gc = capture_sweeps<float>(c, c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, &c->graph32s);
     if (gc == POT3D_OK && precision == POT3D_FP32_REFINED && !serving)
         gc = capture_iterations<float>(c, c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, &c->graph32);
     if (gc != POT3D_OK) {
@@ -1242,10 +1224,10 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
 
 size_t context_bytes(const pot3d_ctx *c)
 {
-    size_t b = (size_t)c->npad * sizeof(double) * (c->r2 ? 5 : 4) + (size_t)c->nt * c->pitch * sizeof(double) +
+    size_t b = (size_t)c->npad * sizeof(double) * 4 + (size_t)c->nt * c->pitch * sizeof(double) +
                (size_t)c->nt * c->np * sizeof(double) + c->rows_h.size() * sizeof(RowCoef) +
                (size_t)kMaxPartials * c->max_blocks * sizeof(double) + (size_t)2 * c->nr * sizeof(double);
-    if (c->precision == POT3D_FP32_REFINED) b += (size_t)c->npad * sizeof(float) * (c->r32b ? 5 : 4);
+    if (c->precision == POT3D_FP32_REFINED) b += (size_t)c->npad * sizeof(float) * 4;
     return b;
 }
 
@@ -1440,13 +1422,12 @@ int pot3d_time_kernels(pot3d_ctx *ctx, int reps, double *ms_update_p, double *ms
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     int rc;
     if (one_sweep(ctx) && ctx->precision == POT3D_FP32_REFINED) {
-        rc = time_sweeps<float>(ctx, ctx->r32, ctx->r32b, ctx->p32[0], ctx->p32[1], ctx->e32, ctx->sc32, reps,
-                                ms_update_p, ms_update_r);
+        rc = time_sweeps<float>(ctx, ctx->r32, ctx->p32[0], ctx->p32[1], ctx->e32, ctx->sc32, reps, ms_update_p,
+                                ms_update_r);
     } else if (ctx->precision == POT3D_FP32_REFINED) {
         rc = time_pair<float>(ctx, ctx->r32, ctx->p32[0], ctx->p32[1], ctx->e32, ctx->sc32, reps, ms_update_p, ms_update_r);
     } else if (one_sweep(ctx)) {
-        rc = time_sweeps<double>(ctx, ctx->r, ctx->r2, ctx->p[0], ctx->p[1], ctx->x, ctx->sc, reps, ms_update_p,
-                                 ms_update_r);
+        rc = time_sweeps<double>(ctx, ctx->r, ctx->p[0], ctx->p[1], ctx->x, ctx->sc, reps, ms_update_p, ms_update_r);
     } else {
         rc = time_pair<double>(ctx, ctx->r, ctx->p[0], ctx->p[1], ctx->x, ctx->sc, reps, ms_update_p, ms_update_r);
     }

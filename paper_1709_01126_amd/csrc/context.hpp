@@ -16,6 +16,7 @@ using pot3d::DevScalars;
 using pot3d::GridArgs;
 using pot3d::RowCoef;
 using pot3d::StencilVecs;
+using pot3d::SweepVecs;
 using pot3d::kTileMarch16;
 using pot3d::kTileMarch8;
 using pot3d::kTileWave2;
@@ -68,8 +69,6 @@ struct pot3d_ctx {
     int iteration = POT3D_ITER_ONE_SWEEP;
     int sweep_rows = 4;           // one-sweep kernel: box rows per wavefront
     GridArgs grid_s{};
-    double *r2 = nullptr;         // one-sweep iteration: the second residual buffer (FP64)
-    float *r32b = nullptr;        // ... (FP32 inner iterations)
     hipGraphExec_t graph_s = nullptr;     // FP64 sweeps
     hipGraphExec_t graph32s = nullptr;    // FP32 inner sweeps
 
@@ -156,7 +155,8 @@ StencilVecs<double> base_vecs(pot3d_ctx *c);
 // b from Br (device) and the starting x (phi0 or zero).
 int prepare_solve(pot3d_ctx *c, const double *br_dev, const double *phi0, hipMemcpyKind kind_in, hipStream_t s);
 // FP64: r = b - A x, p_old = 0, scalars initialised, first residual test.
-int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit);
+// sweeps: the one-sweep iteration follows (r's buffer then holds z = D^-1 r).
+int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit, bool sweeps);
 // Refined: r = b - A x in FP64 and the outer test; waits, then *out holds the scalars.
 int refined_outer_check(pot3d_ctx *c, hipStream_t s, DevScalars *out);
 // Refined: normalised FP32 residual, e = 0, and the inner PCG start (a
@@ -164,7 +164,23 @@ int refined_outer_check(pot3d_ctx *c, hipStream_t s, DevScalars *out);
 // segment `prev`, which ran in normalisation scale_prev).  outer: the scalars
 // of the outer check just made.
 int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left, const DevScalars &outer,
-                        const DevScalars *prev, double scale_prev);
+                        const DevScalars *prev, double scale_prev, bool sweeps);
+// Buffers of the one-sweep iteration: the residual's buffer (z_0 on entry) and
+// the two direction buffers form its ring.
+template <typename V>
+SweepVecs<V> sweep_vecs(V *r, V *p0, V *p1, V *x, DevScalars *sc, double *partial)
+{
+    SweepVecs<V> v{};
+    v.ring[0] = p1;
+    v.ring[1] = r;
+    v.ring[2] = p0;
+    v.x = x;
+    v.sc = sc;
+    v.partial = partial;
+    return v;
+}
+// Whether vectors of the context's grid fit the one-sweep kernel's 32-bit offsets.
+bool sweep_capable(const pot3d_ctx *c);
 // Refined: x += ||r|| e.
 int refined_correct(pot3d_ctx *c, hipStream_t s);
 // True residual, pole values, Phi out, statistics; returns the solve status.

@@ -330,8 +330,8 @@ __device__ __forceinline__ void march_body(const GridArgs &g, const StencilVecs<
                 if (on) {
                     const double bval = (i == 0) ? gbp[CHK((long long)j * g.pitch + k, (long long)nt * g.pitch)] : 0.0;
                     const V res = (V)(bval - (double)ap);
-                    if (v.store_r) gout[idx] = res;
                     const V z = res / diag_at<V>(r_, dph, ihm, ihk);
+                    if (v.store_r) gout[idx] = v.store_r == 2 ? z : res;
                     acc0 += (double)res * (double)z;
                     acc1 += (double)res * (double)res;
                     acc2 += bval * bval;
@@ -715,7 +715,7 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
                 if constexpr (MODE == kApply) {
                     if (row_on) store2(gout, i, j, ap[0], ap[1]);
                 } else if constexpr (MODE == kResidual) {
-                    V res[2];
+                    V res[2], zz[2];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         const double bval = (i == 0 && ve[e] && row_on) ? gbp[CHK((long long)min(j, nt - 1) * g.pitch + (e ? kc1 : kc0), (long long)nt * g.pitch)] : 0.0;
@@ -724,8 +724,9 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
                         acc0 += wrow * ((double)res[e] * (double)z);
                         acc1 += wrow * ((double)res[e] * (double)res[e]);
                         acc2 += bval * bval;
+                        zz[e] = v.store_r == 2 ? z : res[e];
                     }
-                    if (v.store_r && row_on) store2(gout, i, j, res[0], res[1]);
+                    if (v.store_r && row_on) store2(gout, i, j, zz[0], zz[1]);
                 } else if constexpr (MODE == kUpdateP) {
                     acc0 += wrow * ((double)c0 * (double)ap[0] + (double)c1 * (double)ap[1]);
                 } else {  // the r/x update modes
@@ -819,35 +820,43 @@ stencil_wave_batch(const BatchSlot<V> *__restrict__ slots, int nslots)
 
 // ---------------------------------------------------------------------------
 // One-sweep PCG iteration: the Jacobi-PCG of Sec. 2.3 rearranged so that one
-// pass over memory does one iteration (the same iterates in exact arithmetic).
+// pass over memory does one iteration (the same iterates in exact arithmetic),
+// and that pass carries the search directions alone.
 //
 // Sweep j (j = 0, 1, ...) computes
-//   r_j = r_{j-1} - alpha_{j-1} A p_{j-1}    (r_{j-1} and r_j in two buffers)
-//   x_j = x_{j-1} + alpha_{j-1} p_{j-1}      (in place)
-//   z_j = D^-1 r_j,   p_j = z_j + beta_j p_{j-1}
-//   w_j = A p_j                              (not stored)
+//   z_{j-1} = p_{j-1} - beta_{j-1} p_{j-2}          (z = D^-1 r, not stored)
+//   z_j = z_{j-1} - alpha_{j-1} D^-1 A p_{j-1},   r_j = D z_j   (not stored)
+//   x_j = x_{j-1} + alpha_{j-1} p_{j-1}             (in place)
+//   p_j = z_j + beta_j p_{j-1}
+//   w_j = A p_j                                     (not stored)
 // and per-workgroup partial sums of r_j.z_j, r_j.r_j, p_j.w_j, z_j.w_j and
 // w_j.D^-1 w_j.  The finisher then has alpha_j = r_j.z_j / p_j.w_j, and as
 // r_{j+1} = r_j - alpha_j w_j,
 //   r_{j+1}.z_{j+1} = r_j.z_j - 2 alpha_j z_j.w_j + alpha_j^2 w_j.D^-1 w_j,
-// which gives beta_{j+1} before r_{j+1} exists.  Sweep 0 runs with
-// alpha = beta = 0 and p_{-1} = 0.  Traffic: 48 bytes per unknown per
-// iteration (read r, p_old, x; write r, p, x) against 64 for the two passes,
-// and one stencil launch and one finisher instead of two of each.
+// which gives beta_{j+1} before r_{j+1} exists.  Sweep 0 runs with alpha = 0
+// and reads z_0 itself in the place of p_{-2} (beta_{-1} = -1 and a zero
+// factor on p_{-1}).
 //
-// x is needed only at the end, so sweeps can run in pairs that touch it once:
-// an even sweep j leaves x_{j-1} as it is, and the odd sweep j + 1 adds both
-// increments, alpha_{j-1} p_{j-1} + alpha_j p_j.  It has p_j (its p_old) and
-// r_j, hence z_j, and p_j = z_j + beta_j p_{j-1} gives
-// p_{j-1} = (p_j - z_j) / beta_j without reading it: 32 + 48 bytes per
-// unknown per pair of sweeps instead of 2 x 48, with r and p bitwise as
-// before.  z_j is recomputed bitwise (same r_j, same 1/diag), and the
-// rebuilt increment carries a rounding error of about
-// alpha_{j-1} |p_j| eps / beta_j, so the pairing is kept to
-// beta_j >= 1/64; otherwise (and for the restarts, beta = 0) the even sweep
-// updates x itself.  After the last sweep of a solve, x may still lack
-// alpha_{j-1} p_{j-1}; p_{j-1} is then intact in its buffer, and the first
-// workgroup of each sweep records which increment is owed (x_lag).
+// The residual is not kept: the last two directions give z back.  Rebuilding
+// it rounds at about eps |p_{j-1}| per cell; the update that follows already
+// rounds at eps alpha |D^-1 A| |p_{j-1}|, as it does with a stored r, so the
+// residual drifts from b - A x no faster than before (numpy runs of both
+// recurrences at 32 x 64 x 128: true residual 1.20e-12 at the limit in both,
+// the same iteration counts to tolerances of 1e-10 and 1e-13, and of 1e-1 to
+// 1e-4 with FP32 vectors).  Traffic: 24 bytes per unknown per sweep (read two
+// directions, write one), and 16 more when x is read and written, against 32
+// and 16 with r_{j-1} read and r_j written.  Solves with r stored and
+// without, same box: 151 x 301 x 601 FP64 1.495 -> 1.304 s, FP32-refined
+// 0.912 -> 0.803 s; 101 x 201 x 401 0.313 -> 0.265 s; 16 iterations at
+// 301 x 641 x 1281 43.8 -> 36.2 ms.
+//
+// x is needed only at the end, so sweeps run in pairs that touch it once: an
+// even sweep j leaves x_{j-1} as it is, and the odd sweep j + 1 adds both
+// increments, alpha_{j-1} p_{j-1} + alpha_j p_j, from the two directions it
+// reads anyway: 24 + 40 bytes per unknown per pair of sweeps.  After the last
+// sweep of a solve, x may still lack alpha_{j-1} p_{j-1}; p_{j-1} is then
+// intact in its buffer, and the first workgroup of each sweep records which
+// increment is owed (x_lag).
 //
 // p_j feeds A p_j on a one-cell ring around each cell, and A p_{j-1} is
 // needed on that ring too, so p_{j-1} is read with a two-cell ring.  A
@@ -858,13 +867,13 @@ stencil_wave_batch(const BatchSlot<V> *__restrict__ slots, int nslots)
 // and phi neighbours are the neighbouring lanes (DPP shifts).  Wavefront w
 // holds box rows [wR, wR + R).  For each layer a of the chunk, and one layer
 // beyond each end:
-//   stage A, layer a, on the box less its outer ring: A p_{j-1}, r_j, z_j,
+//   stage A, layer a, on the box less its outer ring: A p_{j-1}, z_j, r_j,
 //     p_j (p_{j-1} of layers a-1, a, a+1 from LDS planes);
 //   stage B, layer a - 1, interior: w_j = A p_j and the dot products (p_j of
 //     layers a-2, a-1 from LDS planes, of layer a from registers).
 // Each vector has three LDS layer slots in rotation: one barrier per layer.
-// The row coefficients of three layers are staged in LDS too, and r, x and
-// p_{j-1} of the next layers are loaded one layer ahead.  The coefficients
+// The row coefficients of three layers are staged in LDS too, and p_{j-2}, x
+// and p_{j-1} of the next layers are loaded one layer ahead.  The coefficients
 // are loaded a step before they are written to LDS: a vector-memory wait
 // covers every load issued before it, so writing them in the step that loads
 // them would wait for that step's other loads too.
@@ -881,8 +890,7 @@ __device__ __forceinline__ double recip(double d)
     return __builtin_fma(y, e, y);
 }
 // FP32: the estimate and one Newton step (about an ulp; the IEEE division
-// is three times the instructions).  Both sweeps of a pair use it, so the
-// odd sweep recomputes the even sweep's z bitwise.
+// is three times the instructions).
 __device__ __forceinline__ float recip(float d)
 {
     const float y = __builtin_amdgcn_rcpf(d);
@@ -927,15 +935,7 @@ __device__ __forceinline__ GPtr<T> at_byte(GPtr<T> base, unsigned boff)
 #define SWEEP_AT(base, boff) at_byte((base), (boff))
 #endif
 
-// Whether an even sweep running with alpha_{j-1}, beta_j leaves its x
-// increment to the odd sweep after it (which tests the same values).
-__device__ __forceinline__ bool defer_x(double alpha_prev, double beta)
-{
-    return alpha_prev == 0.0 || (beta >= 1.0 / 64.0 && isfinite(beta));
-}
-
-// LDS of the sweep, one object per (R, V): kernels that inline the body
-// twice (the two x modes of an even sweep) share it.
+// LDS of the sweep, one object per (R, V).
 template <int R, typename V>
 struct alignas(16) SweepLds {   // 16: the coefficient rows are read 16 bytes at a time
     alignas(16) V lp[3][kWaves * R][kWave];     // p_{j-1} of three layers
@@ -952,7 +952,7 @@ __device__ __forceinline__ SweepLds<R, V> &sweep_lds()
 
 template <int R, typename V, int XM>
 __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V> &v, const RowCoef *__restrict__ rows,
-                                           const V *__restrict__ rin, V *__restrict__ rout, const V *__restrict__ pold,
+                                           const V *__restrict__ pold, const V *__restrict__ pold2,
                                            V *__restrict__ pnew, V *__restrict__ xvec, const int b)
 {
     constexpr int ER = kWaves * R;
@@ -967,8 +967,8 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
     if (!v.ignore_done && csc->done) return;   // uniform over the workgroup
     if (v.tstamp && threadIdx.x == 0) atomicMin(&v.tstamp[0], wall_clock64());
 
-    const GPtr<const V> grin = to_global(rin), gpold = to_global(pold);
-    const GPtr<V> grout = to_global(rout), gpnew = to_global(pnew), gx = to_global(xvec);
+    const GPtr<const V> gpold = to_global(pold), gpold2 = to_global(pold2);
+    const GPtr<V> gpnew = to_global(pnew), gx = to_global(xvec);
     const GPtr<const double> gdphi = to_global(g.dphi), gih = to_global(g.ih);
     const GPtr<double> gpart = to_global(v.partial);
 
@@ -1003,15 +1003,11 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
     const V ihk = (V)gih[CHK(kk, np)];
     const V ihs = ihm + ihk;   // the phi part of the diagonal, / pq
     const V alpha = (V)csc->alpha, beta = (V)csc->beta;
-    // x pairing: an even sweep leaves x alone (xskip; the kernel has chosen
-    // this body only if defer_x holds); the odd sweep after it adds
-    // xc (p_{j-1} - z_{j-1}) with xc = alpha_{j-2} / beta_{j-1}.
+    // z_{j-1} = zp p_{j-1} - beta_{j-1} p_{j-2} (zp = 0 in sweep 0, whose p_{-2} is z_0)
+    const V bprev = (V)csc->beta_prev, zp = csc->sweep == 0 ? V(0) : V(1);
+    // x pairing: an even sweep leaves x alone, the odd sweep after it adds both increments
     constexpr bool xskip = XM == 1;
-    V xc = V(0);
-    if (XM == 2) {
-        const double ap = csc->alpha_prev, bp = csc->beta_prev;
-        if (ap != 0.0 && defer_x(ap, bp)) xc = (V)(ap / bp);
-    }
+    const V alpha_p = XM == 2 ? (V)csc->alpha_prev : V(0);
     if (b == 0 && threadIdx.x == 0) {   // the increment x lacks if this is the last sweep
         v.sc->x_lag = xskip ? csc->alpha : 0.0;
         v.sc->x_lag_p = xskip ? (unsigned long long)pold : 0ull;
@@ -1040,14 +1036,14 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
 #pragma unroll
         for (int m = 0; m < R; ++m) dst[m] = *SWEEP_AT(gpold, lb + vrow[m]);
     };
-    // r_{j-1} of layer a; x_{j-1} on the interior of the chunk's own layers
-    auto load_rx = [&](int a, V (&rdst)[R], V (&xdst)[R]) {
+    // p_{j-2} of layer a; x_{j-1} on the interior of the chunk's own layers
+    auto load_px = [&](int a, V (&rdst)[R], V (&xdst)[R]) {
         const bool own = a >= i0 && a < i1;
         const unsigned lb = layer_b(a);
 #pragma unroll
         for (int m = 0; m < R; ++m) {
-            rdst[m] = V(0);   // the box's outer ring needs no r
-            if (e0 + m >= 1 && e0 + m < tjn + 3) rdst[m] = *SWEEP_AT(grin, lb + vrow[m]);
+            rdst[m] = V(0);   // the box's outer ring needs no p_{j-2}
+            if (e0 + m >= 1 && e0 + m < tjn + 3) rdst[m] = *SWEEP_AT(gpold2, lb + vrow[m]);
             xdst[m] = V(0);
             if (!xskip && own && oki[m] && col_in) xdst[m] = stream_load(SWEEP_AT(gx, lb + vrow[m]));
         }
@@ -1095,7 +1091,7 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
 
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0, acc4 = 0.0;
     // One layer step: stage A at layer a, stage B at layer a - 1.  rv, xo:
-    // r_{j-1}, x_{j-1} of layer a (loaded one step ahead; the next layer's go
+    // p_{j-2}, x_{j-1} of layer a (loaded one step ahead; the next layer's go
     // to rv_n, xo_n).  z1, i1: z_j and 1/diag of layer a - 1 (stage B); this
     // step's go to za, ia.  Each wavefront reads its own rows of the LDS
     // planes at any time (it alone writes them) and other rows only across a
@@ -1119,7 +1115,7 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
         __builtin_amdgcn_s_setprio(3);
         if constexpr (kPTwoAhead) load_p(a + 3, pn2);
         else load_p(a + 2, pn);
-        load_rx(a + 1, rv_n, xo_n);
+        load_px(a + 1, rv_n, xo_n);
         cq_n = load_coef(a + 2);
         __builtin_amdgcn_s_setprio(0);
         V qa[R];
@@ -1130,20 +1126,20 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
             const V pc = lp[sa][e][lane];
             const V ap = apply(rc, pc, lp[sb][e][lane], lp[sa1][e][lane], lp[sa][max(e - 1, 0)][lane],
                                lp[sa][min(e + 1, ER - 1)][lane]);
-            const V rn = vfma<V>(-alpha, ap, rv[m]);
-            const V inv = recip(vfma<V>(dph, rc.s, rc.pq * ihs));
-            const V zn = rn * inv;
+            const V d = vfma<V>(dph, rc.s, rc.pq * ihs);
+            const V inv = recip(d);
+            const V zn = vfma<V>(-alpha, ap * inv, vfma<V>(-bprev, rv[m], zp * pc));
             const V qn = vfma<V>(beta, pc, zn);
             qa[m] = qn;
             za[m] = zn;
             ia[m] = inv;
             lq[sa][e][lane] = qn;
             if (own && oki[m] && col_in) {
-                stream_store(SWEEP_AT(grout, lb + vrow[m]), rn);
+                const V rn = zn * d;
                 stream_store(SWEEP_AT(gpnew, lb + vrow[m]), qn);
                 if (!xskip) {
                     V xn = xo[m];
-                    if (XM == 2) xn = vfma<V>(xc, pc - rv[m] * inv, xn);   // alpha_{j-2} p_{j-2}
+                    if (XM == 2) xn = vfma<V>(alpha_p, rv[m], xn);   // alpha_{j-2} p_{j-2}
                     stream_store(SWEEP_AT(gx, lb + vrow[m]), vfma<V>(alpha, pc, xn));
                 }
                 acc0 = __builtin_fma((double)rn, (double)zn, acc0);
@@ -1174,7 +1170,7 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
     V rvA[R], xoA[R], rvB[R], xoB[R], zA[R], iA[R], zB[R], iB[R], pA[R], pB[R];
     put_coef(i0 - 1, load_coef(i0 - 1));
     double cA = load_coef(i0), cB = 0.0;
-    load_rx(i0 - 1, rvA, xoA);
+    load_px(i0 - 1, rvA, xoA);
     {
         V t0[R], t1[R], t2[R];
         load_p(i0 - 2, t0);
@@ -1227,24 +1223,20 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
 }
 #undef SWEEP_AT
 
-// An even sweep (XM = 1) whose alpha_{j-1}, beta_j do not allow the
-// deferral runs the body that updates x itself.  The choice is made once, at
-// the top, between two inlined bodies, so that each keeps exact memory-wait
-// counts (loads under a run-time condition would make the compiler's waits
-// conservative).
+// The ring buffer that sweep j uses as p_{j-off} (off = 0: the one it writes).
+template <typename V>
+__device__ __forceinline__ V *ring_at(const SweepVecs<V> &v, int sweep, int off)
+{
+    const int q = (sweep % 3 + 3 - off) % 3;
+    return q == 0 ? v.ring[0] : (q == 1 ? v.ring[1] : v.ring[2]);
+}
+
 template <int R, typename V, int XM>
 __global__ void __launch_bounds__(kThreads)
-stencil_sweep(GridArgs g, SweepVecs<V> v, const RowCoef *__restrict__ rows, const V *__restrict__ rin,
-              V *__restrict__ rout, const V *__restrict__ pold, V *__restrict__ pnew, V *__restrict__ x)
+stencil_sweep(GridArgs g, SweepVecs<V> v, const RowCoef *__restrict__ rows)
 {
-    if (XM == 1) {
-        const CPtr<const DevScalars> csc = to_const(v.sc);
-        if (!defer_x(csc->alpha, csc->beta)) {
-            sweep_body<R, V, 0>(g, v, rows, rin, rout, pold, pnew, x, blockIdx.x);
-            return;
-        }
-    }
-    sweep_body<R, V, XM>(g, v, rows, rin, rout, pold, pnew, x, blockIdx.x);
+    const int j = to_const(v.sc)->sweep;
+    sweep_body<R, V, XM>(g, v, rows, ring_at(v, j, 1), ring_at(v, j, 2), ring_at(v, j, 0), v.x, blockIdx.x);
 }
 
 // Batched sweeps: slot q owns workgroups [offset, offset + nblocks) of the
@@ -1257,15 +1249,9 @@ stencil_sweep_batch(const BatchSweep<V> *__restrict__ slots, int nslots)
     const int s = batch_slot(slots, nslots, bid);
     if (s < 0) return;
     const BatchSweep<V> sl = slots[s];
-    if (XM == 1) {   // as in stencil_sweep
-        const CPtr<const DevScalars> csc = to_const(sl.v.sc);
-        if (!defer_x(csc->alpha, csc->beta)) {
-            sweep_body<R, V, 0>(sl.g, sl.v, sl.g.rows, sl.v.r_in, sl.v.r_out, sl.v.p_old, sl.v.p_new, sl.v.x,
-                                bid - sl.offset);
-            return;
-        }
-    }
-    sweep_body<R, V, XM>(sl.g, sl.v, sl.g.rows, sl.v.r_in, sl.v.r_out, sl.v.p_old, sl.v.p_new, sl.v.x, bid - sl.offset);
+    const int j = to_const(sl.v.sc)->sweep;
+    sweep_body<R, V, XM>(sl.g, sl.v, sl.g.rows, ring_at(sl.v, j, 1), ring_at(sl.v, j, 2), ring_at(sl.v, j, 0), sl.v.x,
+                         bid - sl.offset);
 }
 
 // ---------------------------------------------------------------------------
@@ -1343,6 +1329,8 @@ __device__ __forceinline__ void finish_body(int which, DevScalars *sc, const dou
         sc->rho = s[0];
         sc->alpha = 0.0;
         sc->beta = 0.0;
+        sc->alpha_prev = 0.0;
+        sc->beta_prev = -1.0;
         sc->k = 0;
         sc->sweep = 0;
         sc->zero_solution = 0;
@@ -1497,6 +1485,8 @@ __device__ __forceinline__ void finish_body(int which, DevScalars *sc, const dou
         sc->bnorm = rnorm;
         sc->alpha = 0.0;
         sc->beta = beta;
+        sc->alpha_prev = 0.0;
+        sc->beta_prev = -1.0;
         sc->k = 0;
         sc->sweep = 0;
         sc->zero_solution = 0;
@@ -1895,15 +1885,16 @@ __global__ void cast_residual_kernel(const double *r64, float *r32, float *e32, 
 
 // Reliable update of the FP32 inner iteration: the true residual replaces the
 // recursive one, the correction restarts from zero, and the last search
-// direction continues in the new units (pdst = f psrc; the two may alias).
+// direction continues in the new units (pdst = f psrc; psrc may be pdst or r32).
 __global__ void resume_residual_kernel(const double *r64, float *r32, float *e32, const float *psrc, float *pdst,
                                        long long n, const DevScalars *sc, float f)
 {
     const double scale = sc->scale;
     for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (long long)gridDim.x * blockDim.x) {
+        const float p = psrc[q];
         r32[q] = (float)(r64[q] * scale);
         e32[q] = 0.0f;
-        pdst[q] = f * psrc[q];
+        pdst[q] = f * p;
     }
 }
 
@@ -1933,9 +1924,10 @@ __global__ void add_correction_kernel(double *x64, const float *e32, long long n
 }
 
 // r.z and r.r of an FP32 vector, one workgroup per group of (i, j) rows taken
-// in a fixed order, one partial per workgroup.
+// in a fixed order, one partial per workgroup.  store_z: z replaces r (the
+// start of the one-sweep iteration).
 __global__ void __launch_bounds__(256)
-dots_rz_kernel(GridArgs g, const float *r, double *partial, int nblocks)
+dots_rz_kernel(GridArgs g, float *r, double *partial, int nblocks, int store_z)
 {
     __shared__ double sh[2][256];
     const int t = threadIdx.x;
@@ -1943,7 +1935,7 @@ dots_rz_kernel(GridArgs g, const float *r, double *partial, int nblocks)
     const int nrows = g.nr * g.nt;
     for (int row = blockIdx.x; row < nrows; row += nblocks) {
         const RowCoef rc = g.rows[row];
-        const float *rp = r + (long long)row * g.pitch;
+        float *rp = r + (long long)row * g.pitch;
         for (int k = t; k < g.np; k += 256) {
             const float dph = (float)g.dphi[k], ihk = (float)g.ih[k];
             const float ihm = (float)g.ih[k == 0 ? g.np - 1 : k - 1];
@@ -1951,6 +1943,7 @@ dots_rz_kernel(GridArgs g, const float *r, double *partial, int nblocks)
             const float z = rv / diag_at<float>(rc, dph, ihm, ihk);
             a0 += (double)rv * (double)z;
             a1 += (double)rv * (double)rv;
+            if (store_z) rp[k] = z;
         }
     }
     sh[0][t] = a0;
@@ -2320,9 +2313,9 @@ template <int R, typename V>
 static void launch_sweep_x(const GridArgs &g, const SweepVecs<V> &v, hipStream_t s)
 {
     const dim3 grid(g.nblocks), block(kThreads);
-    if (v.xmode == 1) stencil_sweep<R, V, 1><<<grid, block, 0, s>>>(g, v, g.rows, v.r_in, v.r_out, v.p_old, v.p_new, v.x);
-    else if (v.xmode == 2) stencil_sweep<R, V, 2><<<grid, block, 0, s>>>(g, v, g.rows, v.r_in, v.r_out, v.p_old, v.p_new, v.x);
-    else stencil_sweep<R, V, 0><<<grid, block, 0, s>>>(g, v, g.rows, v.r_in, v.r_out, v.p_old, v.p_new, v.x);
+    if (v.xmode == 1) stencil_sweep<R, V, 1><<<grid, block, 0, s>>>(g, v, g.rows);
+    else if (v.xmode == 2) stencil_sweep<R, V, 2><<<grid, block, 0, s>>>(g, v, g.rows);
+    else stencil_sweep<R, V, 0><<<grid, block, 0, s>>>(g, v, g.rows);
 }
 
 template <typename V>
@@ -2561,9 +2554,9 @@ hipError_t launch_add_correction(double *x64, const float *e32, long long npad, 
     return hipGetLastError();
 }
 
-hipError_t launch_dots_rz(const GridArgs &g, const float *r, double *partial, int nblocks, hipStream_t s)
+hipError_t launch_dots_rz(const GridArgs &g, float *r, double *partial, int nblocks, bool store_z, hipStream_t s)
 {
-    dots_rz_kernel<<<nblocks, 256, 0, s>>>(g, r, partial, nblocks);
+    dots_rz_kernel<<<nblocks, 256, 0, s>>>(g, r, partial, nblocks, store_z ? 1 : 0);
     return hipGetLastError();
 }
 

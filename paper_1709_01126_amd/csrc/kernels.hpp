@@ -110,7 +110,7 @@ hipError_t launch_repack(const double *src, double *dst, long long nrows, int np
 // r32 = float(r64 * sc->scale); e32 = 0; p32 = 0 (all npad elements)
 hipError_t launch_cast_residual(const double *r64, float *r32, float *e32, float *p32, long long npad,
                                 const DevScalars *sc, hipStream_t s);
-// r32 = float(r64 * sc->scale); e32 = 0; pdst = f * psrc (all npad elements; pdst may be psrc)
+// r32 = float(r64 * sc->scale); e32 = 0; pdst = f * psrc (all npad elements; psrc may be pdst or r32)
 hipError_t launch_resume_residual(const double *r64, float *r32, float *e32, const float *psrc, float *pdst,
                                   long long npad, const DevScalars *sc, float f, hipStream_t s);
 // x64 += double(e32) / sc->scale (all npad elements)
@@ -119,8 +119,8 @@ hipError_t launch_add_correction(double *x64, const float *e32, long long npad, 
 // one increment behind (sweeps with xmode 1 and 2); nothing otherwise.
 template <typename V>
 hipError_t launch_x_catchup(V *x, const DevScalars *sc, int nr, int nt, int np, int pitch, hipStream_t s);
-// per-workgroup partials of r.z and r.r (z = D^-1 r) for an FP32 vector; nblocks <= cap
-hipError_t launch_dots_rz(const GridArgs &g, const float *r, double *partial, int nblocks, hipStream_t s);
+// per-workgroup partials of r.z and r.r (z = D^-1 r) for an FP32 vector; nblocks <= cap; store_z: r becomes z
+hipError_t launch_dots_rz(const GridArgs &g, float *r, double *partial, int nblocks, bool store_z, hipStream_t s);
 
 hipError_t launch_poles(const double *x, const double *dphi, int nr, int nt, int np, int pitch, double period,
                         double *out, hipStream_t s);

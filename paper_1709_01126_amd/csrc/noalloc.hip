@@ -167,8 +167,8 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     double *vt = reinterpret_cast<double *>(base + o_vt);
     double *bplane = reinterpret_cast<double *>(base + o_bpl);
     double *x = reinterpret_cast<double *>(base + o_vec[0]);
-    double *rb[2] = {reinterpret_cast<double *>(base + o_vec[1]), reinterpret_cast<double *>(base + o_vec[2])};
-    double *pb[2] = {reinterpret_cast<double *>(base + o_vec[3]), reinterpret_cast<double *>(base + o_vec[4])};
+    double *r = reinterpret_cast<double *>(base + o_vec[1]);
+    double *pb[2] = {reinterpret_cast<double *>(base + o_vec[2]), reinterpret_cast<double *>(base + o_vec[3])};
     for (GridArgs *g : {&go, &gs}) {
         g->rows = rows;
         g->dphi = dphi;
@@ -192,7 +192,7 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     NA_TRY(hipMemcpyAsync(sc, &h_sc, sizeof(DevScalars), hipMemcpyHostToDevice, s));
 
     // everything that must start at zero (padding included), then b and x
-    for (double *buf : {x, rb[0], rb[1], pb[0], pb[1]}) NA_TRY(launch_fill<double>(buf, shape.npad, 0.0, s));
+    for (double *buf : {x, r, pb[0], pb[1]}) NA_TRY(launch_fill<double>(buf, shape.npad, 0.0, s));
     NA_TRY(launch_fill<double>(bplane, (long long)nt * shape.pitch, 0.0, s));
     NA_TRY(launch_fill<double>(bcs, 4, 0.0, s));
     const bool closed = upper_bc == POT3D_UPPER_CLOSED_WALL;
@@ -201,14 +201,14 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     const size_t rowb = (size_t)np * sizeof(double), pitchb = (size_t)shape.pitch * sizeof(double);
     if (d_phi0) NA_TRY(hipMemcpy2DAsync(x, pitchb, d_phi0, rowb, rowb, (size_t)nr * nt, hipMemcpyDeviceToDevice, s));
 
-    // r = b - A x, the first test; then sweeps (the one-sweep PCG iteration)
+    // r = b - A x, the first test, and z = D^-1 r; then sweeps (the one-sweep PCG iteration)
     StencilVecs<double> rv{};
     rv.sc = sc;
     rv.partial = partial;
     rv.in = x;
-    rv.r = rb[0];
+    rv.r = r;
     rv.bplane = bplane;
-    rv.store_r = 1;
+    rv.store_r = 2;
     rv.ignore_done = 1;
     NA_TRY(launch_stencil<double>(kResidual, kTileWave2, go, rv, s));
     NA_TRY(launch_finish(kFinInit, sc, partial, go.nblocks, s));
@@ -216,14 +216,7 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     long long j = 0;
     for (;;) {
         for (int q = 0; q < kPollSweeps; ++q, ++j) {
-            SweepVecs<double> sv{};
-            sv.r_in = rb[j & 1];
-            sv.r_out = rb[(j + 1) & 1];
-            sv.p_old = pb[j & 1];
-            sv.p_new = pb[(j + 1) & 1];
-            sv.x = x;
-            sv.sc = sc;
-            sv.partial = partial;
+            SweepVecs<double> sv = sweep_vecs<double>(r, pb[0], pb[1], x, sc, partial);
             sv.xmode = sweep_xmode((int)(j & 1));   // x once per pair of sweeps; j starts even
             NA_TRY(launch_sweep<double>(4, gs, sv, s));
             NA_TRY(launch_finish(kFinSweep, sc, partial, gs.nblocks, s));

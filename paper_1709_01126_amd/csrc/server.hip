@@ -124,11 +124,11 @@ struct pot3d_server {
     std::vector<BatchSlot<double>> h_p64[2], h_r64[2];
     std::vector<BatchSlot<float>> h_p32[2], h_r32[2];
     std::vector<BatchFin> h_finp, h_finr;
-    // one-sweep slot tables [parity][slot] (the finishers use d_finp)
-    BatchSweep<double> *d_s64[2] = {nullptr, nullptr};
-    BatchSweep<float> *d_s32[2] = {nullptr, nullptr};
-    std::vector<BatchSweep<double>> h_s64[2];
-    std::vector<BatchSweep<float>> h_s32[2];
+    // one-sweep slot tables [slot] (the finishers use d_finp)
+    BatchSweep<double> *d_s64 = nullptr;
+    BatchSweep<float> *d_s32 = nullptr;
+    std::vector<BatchSweep<double>> h_s64;
+    std::vector<BatchSweep<float>> h_s32;
     DevScalars *h_status = nullptr;   // pinned, [2][slot]: statuses after the two latest replays
     Replay replay[2];
     int last = -1;                    // replay buffer of the most recent launch
@@ -173,16 +173,16 @@ hipError_t dalloc(T **p, size_t count)
 }
 
 template <typename V>
-int capture_batched(pot3d_server *sv, BatchSlot<V> *const *dp, BatchSlot<V> *const *dr, BatchSweep<V> *const *ds,
+int capture_batched(pot3d_server *sv, BatchSlot<V> *const *dp, BatchSlot<V> *const *dr, BatchSweep<V> *ds,
                     int wp, int wr, hipGraphExec_t *out)
 {
     hipStream_t s = sv->capture_stream;
     SV_TRY(sv, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
     if (sv->sweep) {
-        // 2m sweeps: the parity of the r and p buffers continues across replays
+        // 2m sweeps: an even number, so the x pairing continues across replays
         for (int it = 0; it < 2 * sv->graph_m && e == hipSuccess; ++it) {
-            e = launch_sweep_batch<V>(sv->sweep_rows, ds[it & 1], sv->max_slots, wp, sweep_xmode(it), s);
+            e = launch_sweep_batch<V>(sv->sweep_rows, ds, sv->max_slots, wp, sweep_xmode(it), s);
             if (e == hipSuccess) e = launch_finish_batch(kFinSweep, sv->d_finp, sv->max_slots, s);
         }
     }
@@ -250,44 +250,33 @@ void fill_tables(pot3d_server *sv, std::vector<BatchSlot<V>> *hp, std::vector<Ba
         for (int par = 0; par < 2; ++par) {
             hp[par][q] = BatchSlot<V>{};
             hr[par][q] = BatchSlot<V>{};
-            hs[par][q] = BatchSweep<V>{};
         }
+        (*hs)[q] = BatchSweep<V>{};
         sv->h_finp[q] = BatchFin{};
         sv->h_finr[q] = BatchFin{};
         if (!sl.active) continue;
         pot3d_ctx *c = sl.ctx;
-        V *r, *r2, *x, *p[2];
+        V *r, *x, *p[2];
         DevScalars *sc;
         if constexpr (std::is_same<V, double>::value) {
             r = c->r;
-            r2 = c->r2;
             x = c->x;
             p[0] = c->p[0];
             p[1] = c->p[1];
             sc = c->sc;
         } else {
             r = c->r32;
-            r2 = c->r32b;
             x = c->e32;
             p[0] = c->p32[0];
             p[1] = c->p32[1];
             sc = c->sc32;
         }
         if (sv->sweep) {
-            V *rb[2] = {r, r2};
-            for (int par = 0; par < 2; ++par) {
-                BatchSweep<V> &a = hs[par][q];
-                a.g = c->grid_s;
-                a.v.r_in = rb[par];
-                a.v.r_out = rb[par ^ 1];
-                a.v.p_old = p[par];
-                a.v.p_new = p[par ^ 1];
-                a.v.x = x;
-                a.v.sc = sc;
-                a.v.partial = c->partial;
-                a.offset = offp;
-                a.active = 1;
-            }
+            BatchSweep<V> &a = (*hs)[q];
+            a.g = c->grid_s;
+            a.v = sweep_vecs<V>(r, p[0], p[1], x, sc, c->partial);
+            a.offset = offp;
+            a.active = 1;
             sv->h_finp[q] = BatchFin{sc, c->partial, c->grid_s.nblocks, 1};
             offp += round_up(c->grid_s.nblocks, kBlockAlign);
             continue;
@@ -329,25 +318,23 @@ int upload_tables(pot3d_server *sv)
     hipStream_t s = sv->stream;
     const size_t n = sv->max_slots;
     if (sv->precision == POT3D_FP64) {
-        fill_tables<double>(sv, sv->h_p64, sv->h_r64, sv->h_s64);
+        fill_tables<double>(sv, sv->h_p64, sv->h_r64, &sv->h_s64);
         for (int par = 0; par < 2; ++par) {
             SV_TRY(sv, hipMemcpyAsync(sv->d_p64[par], sv->h_p64[par].data(), n * sizeof(BatchSlot<double>),
                                       hipMemcpyHostToDevice, s));
             SV_TRY(sv, hipMemcpyAsync(sv->d_r64[par], sv->h_r64[par].data(), n * sizeof(BatchSlot<double>),
                                       hipMemcpyHostToDevice, s));
-            SV_TRY(sv, hipMemcpyAsync(sv->d_s64[par], sv->h_s64[par].data(), n * sizeof(BatchSweep<double>),
-                                      hipMemcpyHostToDevice, s));
         }
+        SV_TRY(sv, hipMemcpyAsync(sv->d_s64, sv->h_s64.data(), n * sizeof(BatchSweep<double>), hipMemcpyHostToDevice, s));
     } else {
-        fill_tables<float>(sv, sv->h_p32, sv->h_r32, sv->h_s32);
+        fill_tables<float>(sv, sv->h_p32, sv->h_r32, &sv->h_s32);
         for (int par = 0; par < 2; ++par) {
             SV_TRY(sv, hipMemcpyAsync(sv->d_p32[par], sv->h_p32[par].data(), n * sizeof(BatchSlot<float>),
                                       hipMemcpyHostToDevice, s));
             SV_TRY(sv, hipMemcpyAsync(sv->d_r32[par], sv->h_r32[par].data(), n * sizeof(BatchSlot<float>),
                                       hipMemcpyHostToDevice, s));
-            SV_TRY(sv, hipMemcpyAsync(sv->d_s32[par], sv->h_s32[par].data(), n * sizeof(BatchSweep<float>),
-                                      hipMemcpyHostToDevice, s));
         }
+        SV_TRY(sv, hipMemcpyAsync(sv->d_s32, sv->h_s32.data(), n * sizeof(BatchSweep<float>), hipMemcpyHostToDevice, s));
     }
     SV_TRY(sv, hipMemcpyAsync(sv->d_finp, sv->h_finp.data(), n * sizeof(BatchFin), hipMemcpyHostToDevice, s));
     SV_TRY(sv, hipMemcpyAsync(sv->d_finr, sv->h_finr.data(), n * sizeof(BatchFin), hipMemcpyHostToDevice, s));
@@ -396,8 +383,9 @@ int acquire_context(pot3d_server *sv, Request *r, pot3d_ctx **ctx)
             return POT3D_OK;
         }
     }
-    // estimate before allocating: 4 FP64 vectors (+4 or 5 FP32 in refined mode,
-    // +1 FP64 in the FP64 one-sweep form) of the padded size, plus tables
+    // estimate before allocating: 4 FP64 vectors (+4 FP32 in refined mode) of the
+    // padded size, plus tables; one vector more in the one-sweep form, as room
+    // for the tables and sums of the smallest grids
     const long long pitch = (r->np + 7) / 8 * 8;
     const size_t per_cell = sv->precision == POT3D_FP32_REFINED ? (sv->sweep ? 52 : 48) : (sv->sweep ? 40 : 32);
     const size_t need = (size_t)r->nr * r->nt * pitch * per_cell +
@@ -409,7 +397,7 @@ int acquire_context(pot3d_server *sv, Request *r, pot3d_ctx **ctx)
                             sv->precision, sv->device, true, &c);
     if (rc != POT3D_OK) return sfail(sv, rc, pot3d_last_error(nullptr));
     if (c->tile_p != sv->tile_p || c->tile_r != sv->tile_r || c->sweep_rows != sv->sweep_rows ||
-        (sv->sweep && (c->precision == POT3D_FP64 ? !c->r2 : !c->r32b))) {
+        (sv->sweep && !sweep_capable(c))) {
         free_ctx(c);
         return sfail(sv, POT3D_EINVAL, "context launch shape differs from the server's batched kernels");
     }
@@ -470,7 +458,7 @@ int refined_advance(pot3d_server *sv, Slot &sl)
         return retire(sv, sl, out, sl.total_inner, sl.outer);
     }
     SV_CALL(sv, c, refined_start_inner(c, sv->stream, r->tol, r->maxit - sl.total_inner, out,
-                                       sl.outer > 0 ? &sl.last_inner : nullptr, sl.scale_prev));
+                                       sl.outer > 0 ? &sl.last_inner : nullptr, sl.scale_prev, sv->sweep));
     sl.scale_prev = out.scale;
     sl.phase = ++sv->next_phase;
     return POT3D_OK;
@@ -490,7 +478,7 @@ int admit(pot3d_server *sv, Slot &sl, Request *r, pot3d_ctx *c)
     SV_CALL(sv, c, prepare_solve(c, c->br, nullptr, hipMemcpyHostToDevice, s));
     SV_TRY(sv, hipEventRecord(c->ev_loop0, s));
     if (sv->precision == POT3D_FP64) {
-        SV_CALL(sv, c, start_fp64(c, s, r->tol, r->maxit));
+        SV_CALL(sv, c, start_fp64(c, s, r->tol, r->maxit, sv->sweep));
         return POT3D_OK;
     }
     DevScalars init{};
@@ -539,9 +527,9 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
         sv->h_r64[par].assign(max_slots, BatchSlot<double>{});
         sv->h_p32[par].assign(max_slots, BatchSlot<float>{});
         sv->h_r32[par].assign(max_slots, BatchSlot<float>{});
-        sv->h_s64[par].assign(max_slots, BatchSweep<double>{});
-        sv->h_s32[par].assign(max_slots, BatchSweep<float>{});
     }
+    sv->h_s64.assign(max_slots, BatchSweep<double>{});
+    sv->h_s32.assign(max_slots, BatchSweep<float>{});
     sv->h_finp.assign(max_slots, BatchFin{});
     sv->h_finr.assign(max_slots, BatchFin{});
     pot3d_server *p = sv.get();
@@ -560,13 +548,12 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
         if (precision == POT3D_FP64) {
             e = dalloc(&p->d_p64[par], max_slots);
             if (e == hipSuccess) e = dalloc(&p->d_r64[par], max_slots);
-            if (e == hipSuccess) e = dalloc(&p->d_s64[par], max_slots);
         } else {
             e = dalloc(&p->d_p32[par], max_slots);
             if (e == hipSuccess) e = dalloc(&p->d_r32[par], max_slots);
-            if (e == hipSuccess) e = dalloc(&p->d_s32[par], max_slots);
         }
     }
+    if (e == hipSuccess) e = precision == POT3D_FP64 ? dalloc(&p->d_s64, max_slots) : dalloc(&p->d_s32, max_slots);
     if (e == hipSuccess) e = dalloc(&p->d_finp, max_slots);
     if (e == hipSuccess) e = dalloc(&p->d_finr, max_slots);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&p->h_status), 2 * max_slots * sizeof(DevScalars),
@@ -818,8 +805,7 @@ void pot3d_server_destroy(pot3d_server *sv)
     for (auto &g : sv->graphs)
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
     void *bufs[] = {sv->d_p64[0], sv->d_p64[1], sv->d_r64[0], sv->d_r64[1], sv->d_p32[0], sv->d_p32[1],
-                    sv->d_r32[0], sv->d_r32[1], sv->d_s64[0], sv->d_s64[1], sv->d_s32[0], sv->d_s32[1],
-                    sv->d_finp, sv->d_finr};
+                    sv->d_r32[0], sv->d_r32[1], sv->d_s64, sv->d_s32, sv->d_finp, sv->d_finr};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (sv->h_status) (void)hipHostFree(sv->h_status);

@@ -47,9 +47,9 @@ struct alignas(64) DevScalars {
     int sweep;         // one-sweep iteration: sweeps done since the start
     int pad[2];
     double scale;      // refinement: 1 / ||r64|| used to normalise the FP32 residual
-    // One-sweep iteration with x updated every other sweep (SweepVecs::xmode):
-    double alpha_prev; // alpha and beta that the previous sweep ran with
-    double beta_prev;
+    // One-sweep iteration (SweepVecs):
+    double alpha_prev; // alpha and beta that the previous sweep ran with (before the
+    double beta_prev;  // first sweep: 0 and -1, see sweep_body)
     double x_lag;      // alpha of the increment x still lacks after the last sweep (0: none) ...
     unsigned long long x_lag_p;   // ... and the search direction it multiplies (device address)
 };
@@ -95,7 +95,7 @@ struct StencilVecs {
     const double *bplane;  // residual: b on the first radial layer (nt * pitch)
     const DevScalars *sc;
     double *partial;  // [3][nblocks] per-workgroup partial sums
-    int store_r;      // residual: 1 to store r, 0 to reduce only
+    int store_r;      // residual: 1 to store r, 2 to store z = D^-1 r, 0 to reduce only
     int ignore_done;  // 1: run even when sc->done is set
     unsigned long long *tstamp;   // timing runs only: [0] earliest workgroup start, [1] latest
                                   // workgroup end (device wall clock); NULL otherwise
@@ -103,15 +103,14 @@ struct StencilVecs {
                       // preconditioned) instead of r; update-r leaves r.z, r.r to the line pass
 };
 
-// Vectors of one sweep of the one-sweep iteration (sweep j: r_j from r_{j-1}
-// and A p_{j-1}, x_j, p_j; see fused_body).  r and p alternate between two
-// buffers; x is updated in place.
+// Vectors of one sweep of the one-sweep iteration (sweep j: p_j from p_{j-1}
+// and p_{j-2}; see sweep_body).  Sweep j writes ring[j mod 3] and reads
+// p_{j-1} and p_{j-2} from the other two; the kernel takes j from sc->sweep.
+// Before sweep 0, ring[2] holds p_{-1} (zeros, or the direction a refined
+// segment resumes) and ring[1] z_0 = D^-1 r_0.
 template <typename V>
 struct SweepVecs {
-    const V *r_in;    // r_{j-1}
-    V *r_out;         // r_j
-    const V *p_old;   // p_{j-1}
-    V *p_new;         // p_j
+    V *ring[3];
     V *x;             // x_{j-1} in, x_j out
     DevScalars *sc;   // alpha_{j-1}, beta_j (read); x_lag, x_lag_p (written by the first workgroup)
     double *partial;  // [5][nblocks]: r.z, r.r, p.Ap, z.Ap, Ap.D^-1 Ap
@@ -119,7 +118,7 @@ struct SweepVecs {
     unsigned long long *tstamp;   // timing runs only, as in StencilVecs
     int xmode;        // 0: x_j = x_{j-1} + alpha p_{j-1} in every sweep.  Sweeps in pairs:
                       // 1 (even sweeps): x is left for the next sweep; 2 (odd sweeps): x
-                      // takes both increments, p_{j-2} rebuilt as (p_{j-1} - z_{j-1}) / beta_{j-1}
+                      // takes both increments, alpha_{j-2} p_{j-2} + alpha_{j-1} p_{j-1}
 };
 
 // One slot of a batched stencil launch (device-resident table).  `out` is the
