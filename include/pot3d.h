@@ -85,8 +85,10 @@ enum pot3d_iteration {
                                   directions, and x is updated once per pair of sweeps
                                   from them: 32 bytes per unknown per iteration in FP64,
                                   16 in FP32 (40 and 20 with POT3D_SWEEP_X=1 in the
-                                  environment, x every sweep).  The same PCG in exact
-                                  arithmetic.  Default.                                  */
+                                  environment, x every sweep).  Grids whose vectors fit
+                                  the registers and LDS of the chip (up to about 2 million
+                                  cells) run it there instead, in one resident kernel.
+                                  The same PCG in exact arithmetic.  Default.            */
 };
 
 enum pot3d_preconditioner {
@@ -356,7 +358,8 @@ const char *pot3d_version(void);
  *   3. advances every active solve by a fixed number of PCG iterations
  *      (32 sweeps in the one-sweep form, 16 two-pass iterations otherwise;
  *      the form is POT3D_ITERATION's when the server is created, one sweep
- *      by default), all in one replay of one captured HIP graph.
+ *      by default), all in one replay of one captured HIP graph; solves of
+ *      grids that run on chip advance by 256 iterations, one after the other.
  * As in Sec. 3.1, the vectors of a solve stay in device memory from
  * admission to retirement.  Device memory per grid (tables and vectors) is
  * cached and reused by later requests on the same grid.  A solve that has

@@ -609,7 +609,7 @@ void free_ctx(pot3d_ctx *c)
     if (c->stream) (void)hipStreamDestroy(c->stream);
     void *bufs[] = {c->rows, c->dphi, c->ih, c->bfac, c->x, c->r, c->p[0], c->p[1],
                     c->bplane, c->br, c->partial, c->poles, c->vr, c->vt, c->bcs, c->ftab, c->sc,
-                    c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32};
+                    c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32, c->oc.words, c->oc.layers, c->oc.polar, c->oc.faces};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (c->h_sc) (void)hipHostFree(c->h_sc);
@@ -697,16 +697,18 @@ int run_fp64(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream_t 
 {
     const bool line = c->precond == POT3D_PC_PHI_LINE;
     const bool sweep = !line && one_sweep(c);
-    int rc = start_fp64(c, s, tol, maxit, sweep);
+    const bool chip = sweep && c->oc.m > 0;
+    int rc = start_fp64(c, s, tol, maxit, sweep && !chip);
     if (rc != POT3D_OK) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_loop0, s));
     int launches = 0;
     DevScalars fin{};
     hipGraphExec_t graph = line ? c->graph_l : (sweep ? c->graph_s : c->graph);
-    rc = replay_until_done(c, graph, c->sc, s, maxit, sweep ? 2 * c->graph_m : c->graph_m, &launches, &fin);
+    if (chip) rc = run_onchip(c, s, &launches, &fin);
+    else rc = replay_until_done(c, graph, c->sc, s, maxit, sweep ? 2 * c->graph_m : c->graph_m, &launches, &fin);
     if (rc != POT3D_OK) return rc;
     // the increment of x the last sweep or r/x update may have left to a next one
-    HIP_TRY(c, launch_x_catchup<double>(c->x, c->sc, c->nr, c->nt, c->np, c->pitch, s));
+    if (!chip) HIP_TRY(c, launch_x_catchup<double>(c->x, c->sc, c->nr, c->nt, c->np, c->pitch, s));
     HIP_TRY(c, hipEventRecord(c->ev_loop1, s));
     return finish_solve(c, phi_out, kind_out, s, fin, launches, fin.k, 1, line ? two_pass_bytes(false, c->graph_m) + 16.0 : (sweep ? sweep_bytes(false) : two_pass_bytes(false, c->graph_m)), iters,
                         relres_true);
@@ -751,14 +753,16 @@ double inner_tolerance(const pot3d_ctx *c)
     return c->refine_mode == POT3D_REFINE_RELIABLE ? 0.1 : 1e-4;
 }
 
-// sweeps: the segments run in the one-sweep form, which starts from z = D^-1 r
-// and leaves its last direction in another buffer than the two-pass form.
+// form: what the segments run in.  The one-sweep form starts from z = D^-1 r
+// and leaves its last direction in another buffer than the two-pass form; the
+// on-chip kernel leaves beta_k p_{k-1} (its p_k has replaced p_{k-1}), so the
+// new beta is divided by that beta_k, and a beta_k of 0 makes it a restart.
 int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left, const DevScalars &outer,
-                        const DevScalars *prev, double scale_prev, bool sweeps)
+                        const DevScalars *prev, double scale_prev, InnerForm form)
 {
     const int nb_dots = std::max(1, std::min(c->max_blocks, c->nr * c->nt));
     const bool resume = c->refine_mode == POT3D_REFINE_RELIABLE && prev && prev->done && prev->status == POT3D_OK &&
-                        prev->k > 0 &&
+                        prev->k > 0 && (form != kInnerOnchip || prev->beta > 0.0) &&
                         std::isfinite(prev->rho) && prev->rho > 0.0 && scale_prev > 0.0 &&
                         std::isfinite(outer.scale) && outer.scale > 0.0;
     DevScalars in{};
@@ -771,9 +775,12 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
         in.maxit = (int)std::min<long long>(maxit_left, 2LL * prev->k + 64);
         const double f = outer.scale / scale_prev;   // new units per old unit
         const SweepVecs<float> sv = sweep_vecs<float>(c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->partial);
-        const float *last = sweeps ? sv.ring[(prev->k + 2) % 3] : c->p32[prev->k & 1];
+        const float *last = form == kInnerOnchip   ? c->p32[0]
+                            : form == kInnerSweeps ? sv.ring[(prev->k + 2) % 3]
+                                                   : c->p32[prev->k & 1];
         HIP_TRY(c, launch_resume_residual(c->r, c->r32, c->e32, last, c->p32[0], c->npad, c->sc, (float)f, s));
         in.scale = 1.0 / (f * f * prev->rho);   // 1 / rho_prev in the new units
+        if (form == kInnerOnchip) in.scale /= prev->beta;
     } else {
         HIP_TRY(c, launch_cast_residual(c->r, c->r32, c->e32, c->p32[0], c->npad, c->sc, s));
     }
@@ -785,7 +792,7 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
         HIP_TRY(c, launch_finish(resume ? kFinResume : kFinInner, c->sc32, c->partial, c->line_blocks, s));
         return POT3D_OK;
     }
-    HIP_TRY(c, launch_dots_rz(c->grid_o, c->r32, c->partial, nb_dots, sweeps, s));
+    HIP_TRY(c, launch_dots_rz(c->grid_o, c->r32, c->partial, nb_dots, form == kInnerSweeps, s));
     HIP_TRY(c, launch_finish(resume ? kFinResume : kFinInner, c->sc32, c->partial, nb_dots, s));
     return POT3D_OK;
 }
@@ -823,13 +830,16 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
         }
         const bool line = c->precond == POT3D_PC_PHI_LINE;
         const bool sweep = !line && one_sweep(c);
-        rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev, sweep);
+        const bool chip = sweep && c->oc.m > 0;
+        rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev,
+                                 chip ? kInnerOnchip : (sweep ? kInnerSweeps : kInnerTwoPass));
         if (rc != POT3D_OK) return rc;
         scale_prev = out.scale;
-        rc = replay_until_done(c, line ? c->graph32l : (sweep ? c->graph32s : c->graph32), c->sc32, s, maxit - total,
+        if (chip) rc = run_onchip(c, s, &launches, &inner);
+        else rc = replay_until_done(c, line ? c->graph32l : (sweep ? c->graph32s : c->graph32), c->sc32, s, maxit - total,
                                sweep ? 2 * c->graph_m : c->graph_m, &launches, &inner);
         if (rc != POT3D_OK) return rc;
-        HIP_TRY(c, launch_x_catchup<float>(c->e32, c->sc32, c->nr, c->nt, c->np, c->pitch, s));
+        if (!chip) HIP_TRY(c, launch_x_catchup<float>(c->e32, c->sc32, c->nr, c->nt, c->np, c->pitch, s));
         total += inner.k;
         ++outer;
         if (inner.status == POT3D_EBREAKDOWN) {
@@ -851,10 +861,15 @@ int run_solve(pot3d_ctx *c, const double *br_dev, const double *phi0, hipMemcpyK
               hipMemcpyKind kind_out, hipStream_t s, double tol, int maxit, int *iters, double *relres_true)
 {
     HIP_TRY(c, hipEventRecord(c->ev_t0, s));
-    int rc = prepare_solve(c, br_dev, phi0, kind_in, s);
-    if (rc != POT3D_OK) return rc;
-    if (c->precision == POT3D_FP32_REFINED) return run_refined(c, phi_out, kind_out, s, tol, maxit, iters, relres_true);
-    return run_fp64(c, phi_out, kind_out, s, tol, maxit, iters, relres_true);
+    for (;;) {
+        int rc = prepare_solve(c, br_dev, phi0, kind_in, s);
+        if (rc != POT3D_OK) return rc;
+        rc = c->precision == POT3D_FP32_REFINED
+                 ? run_refined(c, phi_out, kind_out, s, tol, maxit, iters, relres_true)
+                 : run_fp64(c, phi_out, kind_out, s, tol, maxit, iters, relres_true);
+        if (rc != kOnchipGaveUp) return rc;
+        c->oc.m = 0;   // the device is not free enough: this context iterates in sweeps from now on
+    }
 }
 
 // Common tail: true residual (FP64), pole values, Phi out, statistics.
@@ -1192,6 +1207,20 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     CREATE_TRY(hipMemsetAsync(c->sc, 0, sizeof(DevScalars), c->stream));
     CREATE_TRY(hipStreamSynchronize(c->stream));
     set_tables(c);
+    c->oc = plan_onchip(c);
+    if (c->oc.m > 0) {
+        CREATE_TRY(dalloc(&c->oc.words, kOnchipWords));
+        CREATE_TRY(launch_fill<double>(reinterpret_cast<double *>(c->oc.words), (long long)kOnchipWords, 0.0, c->stream));
+        std::vector<OnchipLayer> layers((size_t)nr + kOnchipMaxLayers);
+        std::vector<OnchipRow> polar((size_t)nt);
+        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, layers.data(), polar.data());
+        CREATE_TRY(dalloc(&c->oc.layers, layers.size()));
+        CREATE_TRY(dalloc(&c->oc.polar, polar.size()));
+        CREATE_TRY(hipMemcpy(c->oc.layers, layers.data(), layers.size() * sizeof(OnchipLayer), hipMemcpyHostToDevice));
+        CREATE_TRY(hipMemcpy(c->oc.polar, polar.data(), polar.size() * sizeof(OnchipRow), hipMemcpyHostToDevice));
+        CREATE_TRY(hipMalloc(&c->oc.faces, c->oc.face_bytes));
+        CREATE_TRY(hipStreamSynchronize(c->stream));
+    }
     if (precision == POT3D_FP32_REFINED) {
         CREATE_TRY(dalloc(&c->r32, (size_t)c->npad));
         CREATE_TRY(dalloc(&c->p32[0], (size_t)c->npad));
@@ -1224,7 +1253,7 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
 
 size_t context_bytes(const pot3d_ctx *c)
 {
-    size_t b = (size_t)c->npad * sizeof(double) * 4 + (size_t)c->nt * c->pitch * sizeof(double) +
+    size_t b = (size_t)c->npad * sizeof(double) * 4 + c->oc.face_bytes + (size_t)c->nt * c->pitch * sizeof(double) +
                (size_t)c->nt * c->np * sizeof(double) + c->rows_h.size() * sizeof(RowCoef) +
                (size_t)kMaxPartials * c->max_blocks * sizeof(double) + (size_t)2 * c->nr * sizeof(double);
     if (c->precision == POT3D_FP32_REFINED) b += (size_t)c->npad * sizeof(float) * 4;

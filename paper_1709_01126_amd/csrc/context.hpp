@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "onchip.hpp"
 #include "pot3d.h"
 
 using pot3d::BatchFin;
@@ -71,6 +72,9 @@ struct pot3d_ctx {
     GridArgs grid_s{};
     hipGraphExec_t graph_s = nullptr;     // FP64 sweeps
     hipGraphExec_t graph32s = nullptr;    // FP32 inner sweeps
+
+    // One-sweep point-Jacobi iterations of a small grid run on chip
+    pot3d::OnchipPlan oc;
 
     // Preconditioner of single solves (the FP64 iterations, or the FP32 inner
     // ones of the refined mode): point Jacobi (PC1) or the phi-line blocks,
@@ -159,12 +163,14 @@ int prepare_solve(pot3d_ctx *c, const double *br_dev, const double *phi0, hipMem
 int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit, bool sweeps);
 // Refined: r = b - A x in FP64 and the outer test; waits, then *out holds the scalars.
 int refined_outer_check(pot3d_ctx *c, hipStream_t s, DevScalars *out);
+// What runs the FP32 inner iterations: two passes (or the phi-line form), sweeps, or the on-chip kernel.
+enum InnerForm { kInnerTwoPass, kInnerSweeps, kInnerOnchip };
 // Refined: normalised FP32 residual, e = 0, and the inner PCG start (a
 // restart, or in reliable-update mode the continuation of the previous
 // segment `prev`, which ran in normalisation scale_prev).  outer: the scalars
 // of the outer check just made.
 int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left, const DevScalars &outer,
-                        const DevScalars *prev, double scale_prev, bool sweeps);
+                        const DevScalars *prev, double scale_prev, InnerForm form);
 // Buffers of the one-sweep iteration: the residual's buffer (z_0 on entry) and
 // the two direction buffers form its ring.
 template <typename V>

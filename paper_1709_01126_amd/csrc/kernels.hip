@@ -24,6 +24,8 @@
 // fixed order, one partial per workgroup, then a single-workgroup finisher
 // that sums partials in a fixed order.
 #include "kernels.hpp"
+#include "onchip.hpp"
+#include "stencil_ops.hpp"
 
 #include <hip/hip_ext.h>
 
@@ -32,38 +34,6 @@
 #include <type_traits>
 
 namespace pot3d {
-
-// Checked builds (-DPOT3D_CHECKED, libpot3d_checked.so) test every global
-// index of the stencil kernels against its array size.  An index out of range
-// is replaced by 0 and the source line is recorded in g_oob_line, which the
-// host reads after each solve.  Normal builds compile CHK(i, n) to i.
-#ifdef POT3D_CHECKED
-__device__ unsigned int g_oob_line = 0;
-__device__ __forceinline__ long long chk_index(long long i, long long n, unsigned line)
-{
-    if (i < 0 || i >= n) {
-        g_oob_line = line;
-        return 0;
-    }
-    return i;
-}
-#define CHK(i, n) chk_index((long long)(i), (long long)(n), __LINE__)
-#else
-#define CHK(i, n) (i)
-#endif
-
-template <typename V> __device__ __forceinline__ V vfma(V a, V b, V c);
-template <> __device__ __forceinline__ double vfma<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
-template <> __device__ __forceinline__ float vfma<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-// Pointer to global memory, typed as such.
-template <typename T>
-using GPtr = __attribute__((address_space(1))) T *;
-template <typename T>
-__device__ __forceinline__ GPtr<T> to_global(T *p)
-{
-    return (GPtr<T>)p;
-}
 
 // Streaming accesses: vectors that a pass reads or writes once per cell use
 // the non-temporal policy, so they do not displace the lines that are read
@@ -79,16 +49,6 @@ template <typename P, typename T>
 __device__ __forceinline__ void stream_store(P p, T v)
 {
     __builtin_nontemporal_store(v, p);
-}
-
-// Pointer to memory that no kernel writes while this one runs (row tables,
-// the scalar block): uniform loads through it become scalar loads.
-template <typename T>
-using CPtr = __attribute__((address_space(4))) T *;
-template <typename T>
-__device__ __forceinline__ CPtr<T> to_const(T *p)
-{
-    return (CPtr<T>)p;
 }
 
 __device__ __forceinline__ RowCoef load_row(CPtr<const RowCoef> rows, long long idx)
@@ -472,17 +432,6 @@ __device__ __forceinline__ float lane_from_left(float v)
 __device__ __forceinline__ float lane_from_right(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
-}
-
-__device__ __forceinline__ double wave_uniform(double v)
-{
-    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
-    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ float wave_uniform(float v)
-{
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 template <int M, int MODE, typename V>
@@ -878,25 +827,6 @@ stencil_wave_batch(const BatchSlot<V> *__restrict__ slots, int nslots)
 // covers every load issued before it, so writing them in the step that loads
 // them would wait for that step's other loads too.
 // ---------------------------------------------------------------------------
-// Reciprocal of a positive normal value: the hardware estimate refined by
-// two Newton steps y <- y + y (1 - d y), each of which squares the relative
-// error (within about an ulp of 1/d).
-__device__ __forceinline__ double recip(double d)
-{
-    double y = __builtin_amdgcn_rcp(d);
-    double e = __builtin_fma(-d, y, 1.0);
-    y = __builtin_fma(y, e, y);
-    e = __builtin_fma(-d, y, 1.0);
-    return __builtin_fma(y, e, y);
-}
-// FP32: the estimate and one Newton step (about an ulp; the IEEE division
-// is three times the instructions).
-__device__ __forceinline__ float recip(float d)
-{
-    const float y = __builtin_amdgcn_rcpf(d);
-    return __builtin_fmaf(y, __builtin_fmaf(-d, y, 1.0f), y);
-}
-
 // Lane l receives lane l-1 (shr) or l+1 (shl); the lane past the wavefront's
 // end receives 0 (DPP bound control: no initialised destination needed).
 __device__ __forceinline__ double shr1(double v)
@@ -920,15 +850,6 @@ __device__ __forceinline__ float shl1(float v)
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xF, 0xF, true));
 }
 
-// Element at a 32-bit byte offset from a vector's base: the access takes the
-// base in scalar registers and a 32-bit offset per lane.  (The one-sweep
-// path is used for vectors under 4 GiB.)
-template <typename T>
-__device__ __forceinline__ GPtr<T> at_byte(GPtr<T> base, unsigned boff)
-{
-    using C = typename std::conditional<std::is_const<T>::value, const char, char>::type;
-    return (GPtr<T>)((__attribute__((address_space(1))) C *)base + boff);
-}
 #ifdef POT3D_CHECKED
 #define SWEEP_AT(base, boff) ((base) + CHK((boff) / sizeof(V), g.npad))
 #else
@@ -1553,33 +1474,6 @@ __device__ __forceinline__ double powi(double m, int e)
         e >>= 1;
     }
     return r;
-}
-
-// Orders one wavefront's LDS accesses across lanes (a row moving between
-// layouts): release and acquire fences at wavefront scope around a wave barrier.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// A double moved across lanes by a DPP row shift (row_shr:n is 0x110 + n,
-// row_shl:n is 0x100 + n; rows are 16 lanes).  Lanes whose source lies
-// outside their row receive 0.
-template <int CTRL>
-__device__ __forceinline__ double row_shift(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-
-// The value of v in lane l (uniform l), as a wave-uniform double.
-__device__ __forceinline__ double lane_value(double v, int l)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                            __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 // Inclusive scans of affine maps c -> M c + E across the 64 lanes, without
@@ -2502,7 +2396,7 @@ unsigned take_oob_line(hipStream_t s)
         const unsigned zero = 0;
         (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
     }
-    return line;
+    return line ? line : onchip_oob_line();
 #else
     (void)s;
     return 0;

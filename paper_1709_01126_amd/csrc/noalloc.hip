@@ -2,10 +2,11 @@
 //
 // For callers that cannot allocate device memory (code under stream capture,
 // tight serving loops, harnesses that forbid it).  It runs the same kernels
-// as a context's one-sweep FP64 point-Jacobi solve (pot3d_solve_device), but
-// every buffer beyond the caller's inputs and outputs -- the metric tables,
-// the right-hand-side layer, the PCG vectors x, r (two), p (two), the
-// per-workgroup partial sums and the scalar block -- lives in one file-scope
+// as a context's one-sweep FP64 point-Jacobi solve (pot3d_solve_device; on
+// chip where the grid fits there and the exchange fits in the array's rest),
+// but every buffer beyond the caller's inputs and outputs -- the metric tables,
+// the right-hand-side layer, the PCG vectors x, r, p (two), the per-workgroup
+// partial sums and the scalar block -- lives in one file-scope
 // device array, `scratch`, of kScratchBytes.  The tables are built on the host
 // into static staging arrays and copied in.  Nothing here calls hipMalloc,
 // hipFree, hipHostMalloc or graph instantiation: the iterations are launched
@@ -58,6 +59,8 @@ RowCoef h_rows[kMaxRows];
 double h_dphi[kMaxAxis], h_ih[kMaxAxis], h_bfac[kMaxAxis], h_vr[kMaxAxis], h_vt[kMaxAxis];
 double h_work[5 * kMaxAxis];
 DevScalars h_sc;
+OnchipLayer h_layers[kMaxAxis + kOnchipMaxLayers];
+OnchipRow h_polar[kMaxAxis];
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -148,12 +151,24 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     const size_t o_vr = take((size_t)nr * sizeof(double));
     const size_t o_vt = take((size_t)nt * sizeof(double));
     const size_t o_bpl = take((size_t)nt * shape.pitch * sizeof(double));
-    size_t o_vec[5];
+    size_t o_vec[5];   // x, r, p, p; the fifth is the documented limit's, and unused
     for (size_t &o : o_vec) o = take(vec);
     if (off > kScratchBytes)
         return fail(nullptr, POT3D_EINVAL,
                     "grid exceeds the no-allocation limit: " + std::to_string(off) + " bytes of scratch needed, " +
                         std::to_string(kScratchBytes) + " available");
+
+    // the on-chip solve's tables, words and faces, where there is room for them
+    shape.device = dev;
+    shape.oc = plan_onchip(&shape);
+    size_t o_layers = 0, o_polar = 0, o_words = 0, o_faces = 0;
+    if (shape.oc.m > 0) {
+        o_layers = take(((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer));
+        o_polar = take((size_t)nt * sizeof(OnchipRow));
+        o_words = take(kOnchipWords * sizeof(unsigned long long));
+        o_faces = take(shape.oc.face_bytes);
+        if (off > kScratchBytes) shape.oc.m = 0;
+    }
 
     char *base = ds.base;
     DevScalars *sc = reinterpret_cast<DevScalars *>(base + o_sc);
@@ -191,30 +206,70 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     h_sc.maxit = maxit;
     NA_TRY(hipMemcpyAsync(sc, &h_sc, sizeof(DevScalars), hipMemcpyHostToDevice, s));
 
-    // everything that must start at zero (padding included), then b and x
-    for (double *buf : {x, r, pb[0], pb[1]}) NA_TRY(launch_fill<double>(buf, shape.npad, 0.0, s));
-    NA_TRY(launch_fill<double>(bplane, (long long)nt * shape.pitch, 0.0, s));
-    NA_TRY(launch_fill<double>(bcs, 4, 0.0, s));
     const bool closed = upper_bc == POT3D_UPPER_CLOSED_WALL;
-    if (closed) NA_TRY(launch_monopole(d_br, bfac, dphi, nt, np, bcs, s));
-    NA_TRY(launch_rhs(d_br, bfac, dphi, nt, np, shape.pitch, closed ? bcs : nullptr, bplane, s));
     const size_t rowb = (size_t)np * sizeof(double), pitchb = (size_t)shape.pitch * sizeof(double);
-    if (d_phi0) NA_TRY(hipMemcpy2DAsync(x, pitchb, d_phi0, rowb, rowb, (size_t)nr * nt, hipMemcpyDeviceToDevice, s));
-
-    // r = b - A x, the first test, and z = D^-1 r; then sweeps (the one-sweep PCG iteration)
     StencilVecs<double> rv{};
-    rv.sc = sc;
-    rv.partial = partial;
-    rv.in = x;
-    rv.r = r;
-    rv.bplane = bplane;
-    rv.store_r = 2;
-    rv.ignore_done = 1;
-    NA_TRY(launch_stencil<double>(kResidual, kTileWave2, go, rv, s));
-    NA_TRY(launch_finish(kFinInit, sc, partial, go.nblocks, s));
+    auto start = [&](bool chip) -> int {
+        // everything that must start at zero (padding included), then b and x
+        for (double *buf : {x, r, pb[0], pb[1]}) NA_TRY(launch_fill<double>(buf, shape.npad, 0.0, s));
+        NA_TRY(launch_fill<double>(bplane, (long long)nt * shape.pitch, 0.0, s));
+        NA_TRY(launch_fill<double>(bcs, 4, 0.0, s));
+        if (closed) NA_TRY(launch_monopole(d_br, bfac, dphi, nt, np, bcs, s));
+        NA_TRY(launch_rhs(d_br, bfac, dphi, nt, np, shape.pitch, closed ? bcs : nullptr, bplane, s));
+        if (d_phi0) NA_TRY(hipMemcpy2DAsync(x, pitchb, d_phi0, rowb, rowb, (size_t)nr * nt, hipMemcpyDeviceToDevice, s));
+
+        // r = b - A x and the first test; sweeps start from z = D^-1 r
+        rv = StencilVecs<double>{};
+        rv.sc = sc;
+        rv.partial = partial;
+        rv.in = x;
+        rv.r = r;
+        rv.bplane = bplane;
+        rv.store_r = chip ? 1 : 2;
+        rv.ignore_done = 1;
+        NA_TRY(launch_stencil<double>(kResidual, kTileWave2, go, rv, s));
+        NA_TRY(launch_finish(kFinInit, sc, partial, go.nblocks, s));
+        return POT3D_OK;
+    };
+    bool chip = shape.oc.m > 0, done = false;
+    if (chip) {
+        shape.rows = rows;
+        shape.dphi = dphi;
+        shape.ih = ih;
+        shape.x = x;
+        shape.r = r;
+        shape.p[0] = pb[0];
+        shape.p[1] = pb[1];
+        shape.sc = sc;
+        shape.h_sc = &h_sc;
+        shape.oc.layers = reinterpret_cast<OnchipLayer *>(base + o_layers);
+        shape.oc.polar = reinterpret_cast<OnchipRow *>(base + o_polar);
+        shape.oc.words = reinterpret_cast<unsigned long long *>(base + o_words);
+        shape.oc.faces = base + o_faces;
+        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, h_layers, h_polar);
+        NA_TRY(hipMemcpyAsync(shape.oc.layers, h_layers, ((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer), hipMemcpyHostToDevice, s));
+        NA_TRY(hipMemcpyAsync(shape.oc.polar, h_polar, (size_t)nt * sizeof(OnchipRow), hipMemcpyHostToDevice, s));
+        NA_TRY(launch_fill<double>(reinterpret_cast<double *>(shape.oc.words), (long long)kOnchipWords, 0.0, s));
+        rc = start(true);
+        if (rc != POT3D_OK) return rc;
+        int launches = 0;
+        DevScalars out{};
+        rc = run_onchip(&shape, s, &launches, &out);
+        if (rc != POT3D_OK && rc != kOnchipGaveUp) return fail(nullptr, rc, shape.err);
+        done = rc == POT3D_OK;
+        h_sc = DevScalars{};
+        h_sc.tol = tol;
+        h_sc.maxit = maxit;
+        if (!done) NA_TRY(hipMemcpyAsync(sc, &h_sc, sizeof(DevScalars), hipMemcpyHostToDevice, s));
+        if (done) h_sc = out;
+    }
+    if (!done) {
+        rc = start(false);
+        if (rc != POT3D_OK) return rc;
+    }
     const long long max_sweeps = (long long)maxit + 2 * kPollSweeps;
     long long j = 0;
-    for (;;) {
+    while (!done) {
         for (int q = 0; q < kPollSweeps; ++q, ++j) {
             SweepVecs<double> sv = sweep_vecs<double>(r, pb[0], pb[1], x, sc, partial);
             sv.xmode = sweep_xmode((int)(j & 1));   // x once per pair of sweeps; j starts even

@@ -79,6 +79,8 @@ struct Slot {
     unsigned phase = 0;   // bumped whenever the slot's solve (re)starts on the device
     DevScalars last_inner{};   // refined: scalars of the inner segment that just ended
     double scale_prev = 0.0;   // refined: the normalisation that segment ran in
+    bool chip = false;         // iterates in the on-chip kernel, not in the batched graph
+    bool fresh = true;         // ... which has not run since the solve (re)started
 };
 
 // A captured batched graph: launch widths of the two passes, last use.
@@ -97,6 +99,7 @@ struct Replay {
 };
 
 constexpr int kBlockAlign = 8;   // slot offsets keep the XCD of a workgroup unchanged
+constexpr int kChipSteps = 256;  // iterations of an on-chip slot per step (a millisecond or two)
 constexpr int kMaxOvertake = 8;  // later requests that may pass one waiting for streaming budget
 
 int round_up(int v, int a) { return (v + a - 1) / a * a; }
@@ -129,7 +132,7 @@ struct pot3d_server {
     BatchSweep<float> *d_s32 = nullptr;
     std::vector<BatchSweep<double>> h_s64;
     std::vector<BatchSweep<float>> h_s32;
-    DevScalars *h_status = nullptr;   // pinned, [2][slot]: statuses after the two latest replays
+    DevScalars *h_status = nullptr;   // pinned, [3][slot]: statuses after the two latest replays, and of the on-chip slots
     Replay replay[2];
     int last = -1;                    // replay buffer of the most recent launch
     std::vector<BatchGraph> graphs;   // captured batched graphs by launch widths
@@ -254,7 +257,7 @@ void fill_tables(pot3d_server *sv, std::vector<BatchSlot<V>> *hp, std::vector<Ba
         (*hs)[q] = BatchSweep<V>{};
         sv->h_finp[q] = BatchFin{};
         sv->h_finr[q] = BatchFin{};
-        if (!sl.active) continue;
+        if (!sl.active || sl.chip) continue;
         pot3d_ctx *c = sl.ctx;
         V *r, *x, *p[2];
         DevScalars *sc;
@@ -458,9 +461,11 @@ int refined_advance(pot3d_server *sv, Slot &sl)
         return retire(sv, sl, out, sl.total_inner, sl.outer);
     }
     SV_CALL(sv, c, refined_start_inner(c, sv->stream, r->tol, r->maxit - sl.total_inner, out,
-                                       sl.outer > 0 ? &sl.last_inner : nullptr, sl.scale_prev, sv->sweep));
+                                       sl.outer > 0 ? &sl.last_inner : nullptr, sl.scale_prev,
+                                       sl.chip ? kInnerOnchip : (sv->sweep ? kInnerSweeps : kInnerTwoPass)));
     sl.scale_prev = out.scale;
     sl.phase = ++sv->next_phase;
+    sl.fresh = true;
     return POT3D_OK;
 }
 
@@ -471,6 +476,7 @@ int admit(pot3d_server *sv, Slot &sl, Request *r, pot3d_ctx *c)
     sl.ctx = c;
     sl.req = r;
     sl.active = true;
+    sl.chip = sv->sweep && c->oc.m > 0;
     sl.phase = ++sv->next_phase;
     r->t_admit = sv->now();
     SV_TRY(sv, hipEventRecord(c->ev_t0, s));
@@ -478,7 +484,7 @@ int admit(pot3d_server *sv, Slot &sl, Request *r, pot3d_ctx *c)
     SV_CALL(sv, c, prepare_solve(c, c->br, nullptr, hipMemcpyHostToDevice, s));
     SV_TRY(sv, hipEventRecord(c->ev_loop0, s));
     if (sv->precision == POT3D_FP64) {
-        SV_CALL(sv, c, start_fp64(c, s, r->tol, r->maxit, sv->sweep));
+        SV_CALL(sv, c, start_fp64(c, s, r->tol, r->maxit, sv->sweep && !sl.chip));
         return POT3D_OK;
     }
     DevScalars init{};
@@ -556,7 +562,7 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
     if (e == hipSuccess) e = precision == POT3D_FP64 ? dalloc(&p->d_s64, max_slots) : dalloc(&p->d_s32, max_slots);
     if (e == hipSuccess) e = dalloc(&p->d_finp, max_slots);
     if (e == hipSuccess) e = dalloc(&p->d_finr, max_slots);
-    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&p->h_status), 2 * max_slots * sizeof(DevScalars),
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&p->h_status), 3 * max_slots * sizeof(DevScalars),
                                            hipHostMallocDefault);
     if (e != hipSuccess) {
         sfail(nullptr, POT3D_EDEVICE, std::string("server allocation: ") + hipGetErrorString(e));
@@ -617,9 +623,9 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
     // 1. queue the next replay of the active slots (the tables are current),
     //    with a copy of each slot's scalars after it
     int launched = -1;
-    int active = 0;
-    for (const Slot &sl : sv->slots) active += sl.active ? 1 : 0;
-    if (active > 0) {
+    int batched = 0, chips = 0;
+    for (const Slot &sl : sv->slots) (sl.chip ? chips : batched) += sl.active ? 1 : 0;
+    if (batched > 0) {
         const int b = prev == 0 ? 1 : 0;
         hipGraphExec_t g = nullptr;
         const int rc = graph_for(sv, sv->need_p, sv->need_r, &g);
@@ -629,9 +635,9 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         Replay &rp = sv->replay[b];
         for (int q = 0; q < sv->max_slots; ++q) {
             Slot &sl = sv->slots[q];
-            rp.req[q] = sl.active ? sl.req : nullptr;
+            rp.req[q] = sl.active && !sl.chip ? sl.req : nullptr;
             rp.phase[q] = sl.phase;
-            if (!sl.active) continue;
+            if (!rp.req[q]) continue;
             sl.launches += 1;
             DevScalars *src = sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32;
             SV_TRY(sv, hipMemcpyAsync(&sv->h_status[b * sv->max_slots + q], src, sizeof(DevScalars),
@@ -644,6 +650,23 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
     // 2. slots whose current solve ended in the previous replay (the one just
     //    queued is a no-op for them; what follows is ordered after it)
     bool changed = false;
+    auto ended = [&](Slot &sl, const DevScalars &st) -> int {
+        changed = true;
+        if (sv->precision == POT3D_FP64) return retire(sv, sl, st, st.k, 1);
+        sl.total_inner += st.k;
+        sl.outer += 1;
+        sl.last_inner = st;
+        if (st.status == POT3D_EBREAKDOWN) {
+            DevScalars out = st;
+            out.status = POT3D_EBREAKDOWN;
+            return retire(sv, sl, out, sl.total_inner, sl.outer);
+        }
+        if (!sl.chip)
+            SV_TRY(sv, launch_x_catchup<float>(sl.ctx->e32, sl.ctx->sc32, sl.ctx->nr, sl.ctx->nt, sl.ctx->np,
+                                               sl.ctx->pitch, s));
+        SV_CALL(sv, sl.ctx, refined_correct(sl.ctx, s));
+        return refined_advance(sv, sl);
+    };
     if (prev >= 0 && sv->replay[prev].pending) {
         Replay &rp = sv->replay[prev];
         SV_TRY(sv, hipEventSynchronize(rp.done));
@@ -653,27 +676,42 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
             if (!sl.active || rp.req[q] != sl.req || rp.phase[q] != sl.phase) continue;
             const DevScalars st = sv->h_status[prev * sv->max_slots + q];
             if (!st.done) continue;
-            changed = true;
-            if (sv->precision == POT3D_FP64) {
-                const int rc = retire(sv, sl, st, st.k, 1);
-                if (rc != POT3D_OK) return rc;
-                continue;
-            }
-            sl.total_inner += st.k;
-            sl.outer += 1;
-            sl.last_inner = st;
-            if (st.status == POT3D_EBREAKDOWN) {
-                DevScalars out = st;
-                out.status = POT3D_EBREAKDOWN;
-                const int rc = retire(sv, sl, out, sl.total_inner, sl.outer);
-                if (rc != POT3D_OK) return rc;
-                continue;
-            }
-            SV_TRY(sv, launch_x_catchup<float>(sl.ctx->e32, sl.ctx->sc32, sl.ctx->nr, sl.ctx->nt, sl.ctx->np,
-                                               sl.ctx->pitch, s));
-            SV_CALL(sv, sl.ctx, refined_correct(sl.ctx, s));
-            const int rc = refined_advance(sv, sl);
+            const int rc = ended(sl, st);
             if (rc != POT3D_OK) return rc;
+        }
+    }
+    if (chips > 0) {
+        //    small grids advance on chip, one after the other
+        DevScalars *h = sv->h_status + 2 * sv->max_slots;
+        {
+            std::lock_guard<std::mutex> one(onchip_lock(sv->device));
+            for (int q = 0; q < sv->max_slots; ++q) {
+                Slot &sl = sv->slots[q];
+                if (!sl.active || !sl.chip) continue;
+                SV_CALL(sv, sl.ctx, queue_onchip(sl.ctx, kChipSteps, sl.fresh, s));
+                sl.fresh = false;
+                sl.launches += 1;
+                SV_TRY(sv, hipMemcpyAsync(&h[q], sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32,
+                                          sizeof(DevScalars), hipMemcpyDeviceToHost, s));
+            }
+            SV_TRY(sv, hipStreamSynchronize(s));
+        }
+        ++sv->replays;
+        for (int q = 0; q < sv->max_slots; ++q) {
+            Slot &sl = sv->slots[q];
+            if (!sl.active || !sl.chip) continue;
+            if (h[q].gave_up) {   // start again, in the batched sweeps
+                pot3d_ctx *c = sl.ctx;
+                c->oc.m = 0;
+                const double t_admit = sl.req->t_admit;
+                const int rc = admit(sv, sl, sl.req, c);
+                if (rc != POT3D_OK) return rc;
+                if (sl.req) sl.req->t_admit = t_admit;
+                changed = true;
+            } else if (h[q].done) {
+                const int rc = ended(sl, h[q]);
+                if (rc != POT3D_OK) return rc;
+            }
         }
     }
     sv->last = launched;
@@ -732,7 +770,7 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         const int rc = upload_tables(sv);
         if (rc != POT3D_OK) return rc;
     }
-    active = 0;
+    int active = 0;
     for (const Slot &sl : sv->slots) active += sl.active ? 1 : 0;
     if (n_active) *n_active = active;
     if (n_queued) *n_queued = (int)sv->queue.size();

@@ -45,7 +45,8 @@ struct alignas(64) DevScalars {
     int status;        // POT3D_* status once done
     int zero_solution; // ||b|| = 0: the answer is Phi = 0
     int sweep;         // one-sweep iteration: sweeps done since the start
-    int pad[2];
+    int gave_up;       // on-chip solve: an exchange waited too long
+    int pad;
     double scale;      // refinement: 1 / ||r64|| used to normalise the FP32 residual
     // One-sweep iteration (SweepVecs):
     double alpha_prev; // alpha and beta that the previous sweep ran with (before the
