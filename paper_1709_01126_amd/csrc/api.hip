@@ -360,6 +360,16 @@ void choose_launch(pot3d_ctx *c)
     // lines may still sit in the 256 MB memory-side cache.
     c->grid_p.reverse = env_int("POT3D_REVERSE_P", 0) != 0;
     c->grid_r.reverse = env_int("POT3D_REVERSE_R", 1) != 0;
+    // The operator and the preconditioner by themselves work on the caller's
+    // packed rows: the LDS-plane kernel and the row solver access one cell per
+    // lane, so rows need no alignment, and no copies into padded rows are made
+    // (apply at 151 x 301 x 601: 424 us per call with them, 90 without, 4.85 TB/s;
+    // 8-row tiles 95 to 103, 32-row ones 130 to 166, other workgroup counts 90 to 118).
+    c->tile_a = tile_is_wave(c->tile_o) ? kTileMarch16 : c->tile_o;
+    c->grid_a = make_grid(c, c->tile_a, tb > 0 ? tb : std::min(stencil_blocks_per_cu<double>(kApply, c->tile_a), 4) * c->num_cu, 0);
+    c->grid_a.pitch = c->np;
+    c->grid_a.plane = (long long)c->nt * c->np;
+    c->grid_a.npad = c->n;
     c->max_blocks = std::max(c->grid_p.nblocks, std::max(c->grid_r.nblocks, c->grid_o.nblocks));
     if (sweep_capable(c)) {
         // one-sweep kernel: about one resident set of workgroups
@@ -393,7 +403,7 @@ void fill_shape(const pot3d_ctx *c, pot3d_stats &st)
 
 void set_tables(pot3d_ctx *c)
 {
-    for (GridArgs *g : {&c->grid_p, &c->grid_r, &c->grid_o, &c->grid_s}) {
+    for (GridArgs *g : {&c->grid_p, &c->grid_r, &c->grid_o, &c->grid_a, &c->grid_s}) {
         g->rows = c->rows;
         g->dphi = c->dphi;
         g->ih = c->ih;
@@ -650,11 +660,12 @@ int prepare_solve(pot3d_ctx *c, const double *br_dev, const double *phi0, hipMem
     const bool closed = c->upper_bc == POT3D_UPPER_CLOSED_WALL;
     if (closed) HIP_TRY(c, launch_monopole(br_dev, c->bfac, c->dphi, c->nt, c->np, c->bcs, s));
     HIP_TRY(c, launch_rhs(br_dev, c->bfac, c->dphi, c->nt, c->np, c->pitch, closed ? c->bcs : nullptr, c->bplane, s));
-    if (phi0 && kind_in == hipMemcpyHostToDevice && c->pitch != c->np) {
-        // one contiguous host copy into r (free until the solve starts), then
-        // the padded layout on the device
-        HIP_TRY(c, hipMemcpyAsync(c->r, phi0, (size_t)c->n * sizeof(double), kind_in, s));
-        HIP_TRY(c, launch_repack(c->r, c->x, (long long)nrows, c->np, c->pitch, false, s));
+    if (phi0 && kind_in == hipMemcpyHostToDevice) {
+        // one contiguous host copy, of padded rows into r (free until the solve
+        // starts) and from there into the padded layout on the device
+        const bool padded = c->pitch != c->np;
+        HIP_TRY(c, hipMemcpyAsync(padded ? c->r : c->x, phi0, (size_t)c->n * sizeof(double), kind_in, s));
+        if (padded) HIP_TRY(c, launch_repack(c->r, c->x, (long long)nrows, c->np, c->pitch, false, s));
     } else if (phi0) {
         HIP_TRY(c, copy_rows(c->x, pitchb, phi0, rowb, rowb, nrows, kind_in, s));
     }
@@ -890,10 +901,12 @@ int finish_solve(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStrea
     HIP_TRY(c, launch_stencil<double>(kResidual, c->tile_o, c->grid_o, tv, s));
     HIP_TRY(c, launch_finish(kFinTrue, c->sc, c->partial, c->grid_o.nblocks, s));
     HIP_TRY(c, launch_poles(c->x, c->dphi, c->nr, c->nt, c->np, c->pitch, kTwoPi, c->poles, s));
-    if (kind_out == hipMemcpyDeviceToHost && c->pitch != c->np) {
-        // packed on the device into r (no longer needed), then one contiguous copy
-        HIP_TRY(c, launch_repack(c->x, c->r, (long long)nrows, c->np, c->pitch, true, s));
-        HIP_TRY(c, hipMemcpyAsync(phi_out, c->r, (size_t)c->n * sizeof(double), kind_out, s));
+    if (kind_out == hipMemcpyDeviceToHost) {
+        // one contiguous copy (a 2-D copy into pageable memory goes row by row:
+        // 55 ms for the 17 MB of 64 x 128 x 256), of rows packed on the device
+        // into r (no longer needed) where they are padded
+        if (c->pitch != c->np) HIP_TRY(c, launch_repack(c->x, c->r, (long long)nrows, c->np, c->pitch, true, s));
+        HIP_TRY(c, hipMemcpyAsync(phi_out, c->pitch != c->np ? c->r : c->x, (size_t)c->n * sizeof(double), kind_out, s));
     } else {
         HIP_TRY(c, copy_rows(phi_out, rowb, c->x, pitchb, rowb, nrows, kind_out, s));
     }
@@ -1339,15 +1352,11 @@ int pot3d_apply_device(pot3d_ctx *ctx, const double *d_x, double *d_y, void *str
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
-    const size_t rowb = (size_t)ctx->np * sizeof(double), pitchb = (size_t)ctx->pitch * sizeof(double);
-    const size_t nrows = (size_t)ctx->nr * ctx->nt;
-    HIP_TRY(ctx, copy_rows(ctx->p[1], pitchb, d_x, rowb, rowb, nrows, hipMemcpyDeviceToDevice, s));
     StencilVecs<double> a = base_vecs(ctx);
-    a.in = ctx->p[1];
-    a.y = ctx->r;
+    a.in = d_x;
+    a.y = d_y;
     a.ignore_done = 1;
-    HIP_TRY(ctx, launch_stencil<double>(kApply, ctx->tile_o, ctx->grid_o, a, s));
-    HIP_TRY(ctx, copy_rows(d_y, rowb, ctx->r, pitchb, rowb, nrows, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(ctx, launch_stencil<double>(kApply, ctx->tile_a, ctx->grid_a, a, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     if (const unsigned line = take_oob_line(s))
         return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
@@ -1363,17 +1372,10 @@ int pot3d_precondition_device(pot3d_ctx *ctx, const double *d_r, double *d_z, vo
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
-    const size_t rowb = (size_t)ctx->np * sizeof(double), pitchb = (size_t)ctx->pitch * sizeof(double);
-    const size_t nrows = (size_t)ctx->nr * ctx->nt;
-    HIP_TRY(ctx, copy_rows(ctx->r, pitchb, d_r, rowb, rowb, nrows, hipMemcpyDeviceToDevice, s));
-    double *zpad = ctx->p[1];
-    if (ctx->precond == POT3D_PC_PHI_LINE) {
-        zpad = ctx->z;
-        HIP_TRY(ctx, launch_line<double>(ctx->grid_o, ctx->r, zpad, ctx->partial, ctx->line_blocks, ctx->sc, 1, s));
-    } else {
-        HIP_TRY(ctx, launch_jacobi(ctx->grid_o, ctx->r, zpad, s));
-    }
-    HIP_TRY(ctx, copy_rows(d_z, rowb, zpad, pitchb, rowb, nrows, hipMemcpyDeviceToDevice, s));
+    if (ctx->precond == POT3D_PC_PHI_LINE)
+        HIP_TRY(ctx, launch_line<double>(ctx->grid_a, d_r, d_z, ctx->partial, ctx->line_blocks, ctx->sc, 1, s));
+    else
+        HIP_TRY(ctx, launch_jacobi(ctx->grid_a, d_r, d_z, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     if (const unsigned line = take_oob_line(s))
         return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));

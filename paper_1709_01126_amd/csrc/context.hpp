@@ -33,6 +33,8 @@ struct pot3d_ctx {
     int num_cu = 256;
     int graph_m = 16;
     GridArgs grid_p{}, grid_r{}, grid_o{};   // update-p, update-r, other passes
+    int tile_a = kTileMarch16;               // passes over the caller's packed rows
+    GridArgs grid_a{};
 
     int upper_bc = POT3D_UPPER_SOURCE_SURFACE;
     std::vector<double> rf, tf, pf;

@@ -285,7 +285,7 @@ __device__ __forceinline__ void march_body(const GridArgs &g, const StencilVecs<
             const V ap = vfma<V>(dph, t, (V)r_.pq * u);
             const long long idx = on ? CHK(offs(i, j, k), g.npad) : 0;
             if constexpr (MODE == kApply) {
-                if (on) gout[idx] = ap;
+                if (on) stream_store(gout + idx, ap);
             } else if constexpr (MODE == kResidual) {
                 if (on) {
                     const double bval = (i == 0) ? gbp[CHK((long long)j * g.pitch + k, (long long)nt * g.pitch)] : 0.0;
@@ -661,9 +661,7 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
                     u = vfma<V>(ihk[e], cc[e] - kp[e], u);
                     ap[e] = ve[e] ? vfma<V>(dph[e], t, (V)r_.pq * u) : V(0);
                 }
-                if constexpr (MODE == kApply) {
-                    if (row_on) store2(gout, i, j, ap[0], ap[1]);
-                } else if constexpr (MODE == kResidual) {
+                if constexpr (MODE == kResidual) {
                     V res[2], zz[2];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
@@ -1691,7 +1689,7 @@ line_solve_kernel(GridArgs g, const V *__restrict__ rin, V *__restrict__ zout, d
     }
 }
 
-// Point Jacobi, z = D^-1 r over the padded layout (padding stays zero).
+// Point Jacobi, z = D^-1 r (rows of g.pitch).
 __global__ void __launch_bounds__(256)
 jacobi_kernel(GridArgs g, const double *__restrict__ r, double *__restrict__ z)
 {
@@ -1975,56 +1973,65 @@ __global__ void __launch_bounds__(256) gauge_mean_kernel(const double *partial, 
 //   Bt nr x (nt+1) x np:  -(Phi_j - Phi_{j-1}) ft_j / r_i (ft = 0 on the poles);
 //   Bp nr x nt x np (faces k+1/2):  -(Phi_{k+1} - Phi_k) ih_k / (r_i sin(theta_j)).
 // fr, ft: inverse centre spacings; rinv = 1 / r_i; sinv = 1 / sin(theta_j).
-// One workgroup per output row (a phi row of one component); the row decode
-// is uniform and the lanes stream along phi.
+// Bound by its bytes: x read once and three fields written, 32 bytes per cell.
+// A wavefront owns 64 azimuthal cells of one polar row and walks a chunk of
+// layers, so Phi_{i-1} stays in a register; Phi_{k+1} comes from the next lane
+// and Phi_{j-1} from the row that the next wavefront of the workgroup reads.
+// The next layer's loads are issued a layer ahead.  310 us per call at
+// 151 x 301 x 601 with one workgroup per output row, which read x five times,
+// 259 so (3.4 TB/s: three of the four streams are writes); 256 cells per
+// wavefront, whose stores share fewer lines, took 264.
+// Polar row nt has the last theta-face only.
 __global__ void __launch_bounds__(256) field_kernel(const double *x, const double *bplane, const double *bfac,
                                                     const double *dphi, const double *ih, const double *fr,
                                                     const double *ft, const double *rinv, const double *sinv, int nr,
-                                                    int nt, int np, int pitch, double *bfr, double *bft, double *bfp)
+                                                    int nt, int np, int pitch, int ci, double *bfr, double *bft,
+                                                    double *bfp)
 {
-    const long long rows_r = (long long)(nr + 1) * nt, rows_t = (long long)nr * (nt + 1);
-    const long long rows = rows_r + rows_t + (long long)nr * nt;
-    const int t = threadIdx.x;
-    auto xrow = [&](int i, int j) { return x + ((long long)i * nt + j) * pitch; };
-    for (long long row = blockIdx.x; row < rows; row += gridDim.x) {
-        if (row < rows_r) {
-            const int i = (int)(row / nt), j = (int)(row % nt);
-            double *out = bfr + row * np;
-            if (i == 0) {
-                const double *bp = bplane + (long long)j * pitch;
-                const double bj = bfac[j];
-                for (int k = t; k < np; k += 256) out[k] = bp[k] / (dphi[k] * bj);
-            } else if (i == nr) {
-                const double *xa = xrow(nr - 1, j);
-                const double f = fr[nr];
-                for (int k = t; k < np; k += 256) out[k] = xa[k] * f;
-            } else {
-                const double *xa = xrow(i, j), *xb = xrow(i - 1, j);
-                const double f = fr[i];
-                for (int k = t; k < np; k += 256) out[k] = -(xa[k] - xb[k]) * f;
-            }
-        } else if (row < rows_r + rows_t) {
-            const long long u = row - rows_r;
-            const int i = (int)(u / (nt + 1)), j = (int)(u % (nt + 1));
-            double *out = bft + u * np;
-            if (j == 0 || j == nt) {
-                for (int k = t; k < np; k += 256) out[k] = 0.0;
-            } else {
-                const double *xa = xrow(i, j), *xb = xrow(i, j - 1);
-                const double f = ft[j] * rinv[i];
-                for (int k = t; k < np; k += 256) out[k] = -(xa[k] - xb[k]) * f;
-            }
-        } else {
-            const long long u = row - rows_r - rows_t;
-            const int i = (int)(u / nt), j = (int)(u % nt);
-            double *out = bfp + u * np;
-            const double *xa = xrow(i, j);
-            const double f = rinv[i] * sinv[j];
-            for (int k = t; k < np; k += 256) {
-                const int kp = (k == np - 1) ? 0 : k + 1;
-                out[k] = -(xa[kp] - xa[k]) * ih[k] * f;
-            }
+    const GPtr<const double> gx = to_global(x);
+    const GPtr<double> gr = to_global(bfr), gt = to_global(bft), gp = to_global(bfp);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nseg = (np + kWave - 1) / kWave, njt = (nt + 1 + kWaves - 1) / kWaves;
+    // the tiles of a stretch of rows on one XCD (as in march_body): the fields'
+    // rows are packed, so the lines at the ends of a tile's stores are shared
+    const int per = gridDim.x / kXcds, bid = blockIdx.x;
+    const int L = bid < per * kXcds ? (bid % kXcds) * per + bid / kXcds : bid;
+    const int seg = L % nseg, jt = (L / nseg) % njt, ic = L / (nseg * njt);
+    const int j = jt * kWaves + w;
+    if (j > nt) return;
+    const int k = seg * kWave + lane;
+    const bool on = k < np;
+    const int kc = min(k, np - 1);
+    const int i0 = ic * ci, i1 = min(i0 + ci, nr);
+    const long long plane = (long long)nt * pitch;
+    if (j == nt) {
+        for (int i = i0; i < i1; ++i)
+            if (on) stream_store(gt + ((long long)i * (nt + 1) + nt) * np + k, 0.0);
+        return;
+    }
+    const GPtr<const double> row = gx + (long long)j * pitch + kc, south = j > 0 ? row - pitch : row;
+    const GPtr<const double> wrap = gx + (long long)j * pitch + (seg * kWave + kWave < np ? seg * kWave + kWave : 0);
+    const bool edge = k == np - 1 || lane == kWave - 1;   // whose phi neighbour is another segment's
+    const double ftj = ft[j], sj = sinv[j], ihk = ih[kc];
+    double below = i0 > 0 ? row[(long long)(i0 - 1) * plane] : 0.0;
+    double c = row[i0 * plane], cs = south[i0 * plane], ce = wrap[i0 * plane];
+    for (int i = i0; i < i1; ++i) {
+        const long long in = (long long)min(i + 1, nr - 1) * plane;
+        const double n = row[in], ns = south[in], ne = wrap[in];
+        const double next = lane_from_right(c), right = edge ? ce : next;
+        const double ri = rinv[i];
+        if (on) {
+            const double br = i == 0 ? to_global(bplane)[(long long)j * pitch + k] / (dphi[k] * bfac[j]) : -(c - below) * fr[i];
+            stream_store(gr + ((long long)i * nt + j) * np + k, br);
+            stream_store(gt + ((long long)i * (nt + 1) + j) * np + k, j == 0 ? 0.0 : -(c - cs) * (ftj * ri));
+            stream_store(gp + ((long long)i * nt + j) * np + k, -(right - c) * ihk * (ri * sj));
+            if (i == nr - 1) stream_store(gr + ((long long)nr * nt + j) * np + k, c * fr[nr]);
         }
+        below = c;
+        c = n;
+        cs = ns;
+        ce = ne;
     }
 }
 
@@ -2137,7 +2144,6 @@ static hipError_t launch_wave(int mode, const GridArgs &g, const StencilVecs<V> 
 {
     V *out = out_vector(mode, v);
     switch (mode) {
-    case kApply: return launch_kernel(stencil_wave<M, kApply, V>, g, v, out, s, e0, e1);
     case kResidual: return launch_kernel(stencil_wave<M, kResidual, V>, g, v, out, s, e0, e1);
     case kUpdateP: return launch_kernel(stencil_wave<M, kUpdateP, V>, g, v, out, s, e0, e1);
     case kUpdateR: return launch_kernel(stencil_wave<M, kUpdateR, V>, g, v, out, s, e0, e1);
@@ -2167,13 +2173,20 @@ static const void *stencil_symbol(int mode, int tile)
 {
 #define POT3D_SYM(K, T)                                                                                 \
     switch (mode) {                                                                                      \
-    case kApply: return reinterpret_cast<const void *>(&K<T, kApply, V>);                                \
     case kResidual: return reinterpret_cast<const void *>(&K<T, kResidual, V>);                          \
     case kUpdateP: return reinterpret_cast<const void *>(&K<T, kUpdateP, V>);                            \
     case kUpdateR: return reinterpret_cast<const void *>(&K<T, kUpdateR, V>);                            \
     case kUpdateRSkip: return reinterpret_cast<const void *>(&K<T, kUpdateRSkip, V>);                    \
     case kUpdateRPair: return reinterpret_cast<const void *>(&K<T, kUpdateRPair, V>);                    \
     default: return nullptr;                                                                             \
+    }
+    if (mode == kApply) {   // LDS-plane kernels only
+        switch (tile) {
+        case kTileMarch8: return reinterpret_cast<const void *>(&stencil_march<8, kApply, V>);
+        case kTileMarch16: return reinterpret_cast<const void *>(&stencil_march<16, kApply, V>);
+        case kTileMarch32: return reinterpret_cast<const void *>(&stencil_march<32, kApply, V>);
+        default: return nullptr;
+        }
     }
     switch (tile) {
     case kTileMarch8: POT3D_SYM(stencil_march, 8)
@@ -2341,9 +2354,12 @@ hipError_t launch_field(const double *x, const double *bplane, const double *bfa
                         const double *fr, const double *ft, const double *rinv, const double *sinv, int nr, int nt,
                         int np, int pitch, double *bfr, double *bft, double *bfp, hipStream_t s)
 {
-    const long long rows = (long long)(nr + 1) * nt + (long long)nr * (nt + 1) + (long long)nr * nt;
-    const unsigned grid = (unsigned)std::min<long long>(rows, 1LL << 20);
-    field_kernel<<<grid, 256, 0, s>>>(x, bplane, bfac, dphi, ih, fr, ft, rinv, sinv, nr, nt, np, pitch, bfr, bft, bfp);
+    const long long tiles = (long long)((np + kWave - 1) / kWave) * ((nt + 1 + kWaves - 1) / kWaves);
+    // chunks of layers: enough workgroups to fill the chip several times over, at least 8 layers each
+    const int want = (int)std::max<long long>(1, std::min<long long>((8192 + tiles - 1) / tiles, std::max(1, nr / 8)));
+    const int ci = (nr + want - 1) / want;
+    const unsigned grid = (unsigned)(tiles * ((nr + ci - 1) / ci));
+    field_kernel<<<grid, kThreads, 0, s>>>(x, bplane, bfac, dphi, ih, fr, ft, rinv, sinv, nr, nt, np, pitch, ci, bfr, bft, bfp);
     return hipGetLastError();
 }
 
