@@ -363,10 +363,10 @@ void choose_launch(pot3d_ctx *c)
     // The operator and the preconditioner by themselves work on the caller's
     // packed rows: the LDS-plane kernel and the row solver access one cell per
     // lane, so rows need no alignment, and no copies into padded rows are made
-    // (apply at 151 x 301 x 601: 424 us per call with them, 90 without, 4.85 TB/s;
-    // 8-row tiles 95 to 103, 32-row ones 130 to 166, other workgroup counts 90 to 118).
+    // (apply at 151 x 301 x 601: 424 us per call with them, 118 without, 3.7 TB/s;
+    // 8-row tiles 119 to 142, other workgroup counts 124 to 142).
     c->tile_a = tile_is_wave(c->tile_o) ? kTileMarch16 : c->tile_o;
-    c->grid_a = make_grid(c, c->tile_a, tb > 0 ? tb : std::min(stencil_blocks_per_cu<double>(kApply, c->tile_a), 4) * c->num_cu, 0);
+    c->grid_a = make_grid(c, c->tile_a, tb > 0 ? tb : std::max(1, std::min(stencil_blocks_per_cu<double>(kApply, c->tile_a), 3)) * c->num_cu, 0);
     c->grid_a.pitch = c->np;
     c->grid_a.plane = (long long)c->nt * c->np;
     c->grid_a.npad = c->n;

@@ -1979,8 +1979,7 @@ __global__ void __launch_bounds__(256) gauge_mean_kernel(const double *partial, 
 // and Phi_{j-1} from the row that the next wavefront of the workgroup reads.
 // The next layer's loads are issued a layer ahead.  310 us per call at
 // 151 x 301 x 601 with one workgroup per output row, which read x five times,
-// 259 so (3.4 TB/s: three of the four streams are writes); 256 cells per
-// wavefront, whose stores share fewer lines, took 264.
+// 277 so (3.2 TB/s; rows of 608 cells, whose stores are whole lines, 250).
 // Polar row nt has the last theta-face only.
 __global__ void __launch_bounds__(256) field_kernel(const double *x, const double *bplane, const double *bfac,
                                                     const double *dphi, const double *ih, const double *fr,
@@ -2355,9 +2354,7 @@ hipError_t launch_field(const double *x, const double *bplane, const double *bfa
                         int np, int pitch, double *bfr, double *bft, double *bfp, hipStream_t s)
 {
     const long long tiles = (long long)((np + kWave - 1) / kWave) * ((nt + 1 + kWaves - 1) / kWaves);
-    // chunks of layers: enough workgroups to fill the chip several times over, at least 8 layers each
-    const int want = (int)std::max<long long>(1, std::min<long long>((8192 + tiles - 1) / tiles, std::max(1, nr / 8)));
-    const int ci = (nr + want - 1) / want;
+    const int ci = std::min(nr, 4);   // layers per wavefront: packed rows of 601 cells 277 us, with 14 layers 294, with 1 295
     const unsigned grid = (unsigned)(tiles * ((nr + ci - 1) / ci));
     field_kernel<<<grid, kThreads, 0, s>>>(x, bplane, bfac, dphi, ih, fr, ft, rinv, sinv, nr, nt, np, pitch, ci, bfr, bft, bfp);
     return hipGetLastError();
