@@ -384,6 +384,34 @@ void choose_launch(pot3d_ctx *c)
     }
 }
 
+// Launch of the phi-line iteration: at most one set of resident workgroups,
+// which share the items (a chunk of ci layers of four polar rows) in rounds.
+// ci is the one whose rounds walk the fewest layers, counting one more per item
+// for its start, which loads two layers that no round before has left in
+// registers.
+void choose_line_grid(pot3d_ctx *c, int per_cu)
+{
+    const long long resident = std::min<long long>(c->max_blocks, (long long)std::max(1, per_cu) * std::max(1, c->num_cu));
+    GridArgs g = c->grid_o;
+    g.ntj = (c->nt + kWaves - 1) / kWaves;
+    long long best = -1;
+    for (int ci = 1; ci <= c->nr; ++ci) {
+        const long long nchunk = (c->nr + ci - 1) / ci, items = nchunk * g.ntj;
+        const long long walk = (items + resident - 1) / resident * (ci + 1);
+        if (best >= 0 && walk >= best) continue;
+        best = walk;
+        g.ci = ci;
+        g.nchunk = (int)nchunk;
+        g.nblocks = (int)std::min(items, resident);
+    }
+    if (const int ci = env_int("POT3D_LINE_CI", 0); ci > 0) {   // launch-shape experiments
+        g.ci = std::min(ci, c->nr);
+        g.nchunk = (c->nr + g.ci - 1) / g.ci;
+        g.nblocks = (int)std::min<long long>((long long)g.nchunk * g.ntj, resident);
+    }
+    c->grid_l = g;
+}
+
 void fill_shape(const pot3d_ctx *c, pot3d_stats &st)
 {
     st.tile_p = c->tile_p;
@@ -496,12 +524,13 @@ double two_pass_bytes(bool fp32, int m)
     return fp32 ? b / 2 : b;
 }
 
-// Capture 2 m sweeps of the one-sweep iteration (sweep, finisher) on the
+// Capture 2 m sweeps of the one-sweep iteration (sweep, finisher; line: the
+// two kernels of the phi-line iteration, whose residual buffer is z's) on the
 // idle context stream.  The sweeps take their place in the ring of three
 // direction buffers from the device's sweep count; 2 m is even, so replays
 // continue the x pairing (an even sweep leaves x to the odd one after it).
 template <typename V>
-int capture_sweeps(pot3d_ctx *c, V *r, V *p0, V *p1, V *x, DevScalars *sc, hipGraphExec_t *out)
+int capture_sweeps(pot3d_ctx *c, V *r, V *p0, V *p1, V *x, DevScalars *sc, bool line, hipGraphExec_t *out)
 {
     hipStream_t s = c->stream;
     HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
@@ -509,57 +538,11 @@ int capture_sweeps(pot3d_ctx *c, V *r, V *p0, V *p1, V *x, DevScalars *sc, hipGr
     for (int it = 0; it < 2 * c->graph_m && e == hipSuccess; ++it) {
         SweepVecs<V> v = sweep_vecs<V>(r, p0, p1, x, sc, c->partial);
         v.xmode = sweep_xmode(it);
-        e = launch_sweep<V>(c->sweep_rows, c->grid_s, v, s);
-        if (e == hipSuccess) e = launch_finish(kFinSweep, sc, c->partial, c->grid_s.nblocks, s);
-    }
-    hipGraph_t graph = nullptr;
-    hipError_t e2 = hipStreamEndCapture(s, &graph);
-    if (e != hipSuccess) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return fail(c, POT3D_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-    }
-    if (e2 != hipSuccess) return fail(c, POT3D_EDEVICE, std::string("hipStreamEndCapture: ") + hipGetErrorString(e2));
-    hipError_t e3 = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e3 != hipSuccess) return fail(c, POT3D_EDEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e3));
-    return POT3D_OK;
-}
-
-// Capture m PCG iterations with the phi-line block preconditioner: the
-// direction update on z (p = z + beta p_old, A p, p.Ap), alpha, the r/x
-// update, the line pass (z = M^-1 r, r.z, r.r), then beta and convergence.
-// V: the vector type (FP64 solves, or the FP32 inner iterations of the
-// refined mode, whose scalars and sums stay FP64).
-template <typename V>
-int capture_line_iterations(pot3d_ctx *c, V *r, V *p0, V *p1, V *x, V *z, DevScalars *sc, hipGraphExec_t *out)
-{
-    hipStream_t s = c->stream;
-    HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    hipError_t e = hipSuccess;
-    V *pb[2] = {p0, p1};
-    for (int it = 0; it < c->graph_m && e == hipSuccess; ++it) {
-        StencilVecs<V> a{};
-        a.sc = sc;
-        a.partial = c->partial;
-        a.in = z;
-        a.pold = pb[it & 1];
-        a.pnew = pb[(it + 1) & 1];
-        a.zin = 1;
-        e = launch_stencil<V>(kUpdateP, c->tile_p, c->grid_p, a, s);
-        if (e == hipSuccess) e = launch_finish(kFinSigma, sc, c->partial, c->grid_p.nblocks, s);
-        if (e == hipSuccess) {
-            StencilVecs<V> bv{};
-            bv.sc = sc;
-            bv.partial = c->partial;
-            bv.in = pb[(it + 1) & 1];
-            bv.pold = pb[it & 1];   // p_{k-1}, for the odd r/x update of a pair
-            bv.r = r;
-            bv.x = x;
-            bv.zin = 1;
-            e = launch_stencil<V>(update_r_mode(it, c->graph_m), c->tile_r, c->grid_r, bv, s);
-        }
-        if (e == hipSuccess) e = launch_line<V>(c->grid_o, r, z, c->partial, c->line_blocks, sc, 0, s);
-        if (e == hipSuccess) e = launch_finish(kFinRho, sc, c->partial, c->line_blocks, s);
+        e = line ? launch_line_iteration<V>(c->grid_l, v, s)
+                 : launch_sweep<V>(c->sweep_rows, c->grid_s, v, s);
+        if (e == hipSuccess)
+            e = line ? launch_finish(kFinLine, sc, c->partial, c->grid_l.nblocks, s)
+                     : launch_finish(kFinSweep, sc, c->partial, c->grid_s.nblocks, s);
     }
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(s, &graph);
@@ -695,7 +678,7 @@ int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit, bool sweeps)
     if (c->precond == POT3D_PC_PHI_LINE) {
         // z = M^-1 r of the starting residual and rho = r.z (the first
         // direction update then forms p = z)
-        HIP_TRY(c, launch_line<double>(c->grid_o, c->r, c->z, c->partial, c->line_blocks, c->sc, 1, s));
+        HIP_TRY(c, launch_line<double>(c->grid_o, c->r, c->z, c->partial, c->line_blocks, s));
         HIP_TRY(c, launch_finish(kFinLineInit, c->sc, c->partial, c->line_blocks, s));
     }
     return POT3D_OK;
@@ -716,7 +699,7 @@ int run_fp64(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream_t 
     DevScalars fin{};
     hipGraphExec_t graph = line ? c->graph_l : (sweep ? c->graph_s : c->graph);
     if (chip) rc = run_onchip(c, s, &launches, &fin);
-    else rc = replay_until_done(c, graph, c->sc, s, maxit, sweep ? 2 * c->graph_m : c->graph_m, &launches, &fin);
+    else rc = replay_until_done(c, graph, c->sc, s, maxit, sweep || line ? 2 * c->graph_m : c->graph_m, &launches, &fin);
     if (rc != POT3D_OK) return rc;
     // the increment of x the last sweep or r/x update may have left to a next one
     if (!chip) HIP_TRY(c, launch_x_catchup<double>(c->x, c->sc, c->nr, c->nt, c->np, c->pitch, s));
@@ -785,9 +768,9 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
         // a capped segment (status ENOCONV) makes the next one a restart.
         in.maxit = (int)std::min<long long>(maxit_left, 2LL * prev->k + 64);
         const double f = outer.scale / scale_prev;   // new units per old unit
-        const SweepVecs<float> sv = sweep_vecs<float>(c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->partial);
+        const SweepVecs<float> sv = sweep_vecs<float>(form == kInnerLine ? c->z32 : c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->partial);
         const float *last = form == kInnerOnchip   ? c->p32[0]
-                            : form == kInnerSweeps ? sv.ring[(prev->k + 2) % 3]
+                            : form != kInnerTwoPass ? sv.ring[(prev->k + 2) % 3]
                                                    : c->p32[prev->k & 1];
         HIP_TRY(c, launch_resume_residual(c->r, c->r32, c->e32, last, c->p32[0], c->npad, c->sc, (float)f, s));
         in.scale = 1.0 / (f * f * prev->rho);   // 1 / rho_prev in the new units
@@ -799,7 +782,7 @@ int refined_start_inner(pot3d_ctx *c, hipStream_t s, double tol, int maxit_left,
     HIP_TRY(c, hipMemcpyAsync(c->sc32, &c->h_sc[1], sizeof(DevScalars), hipMemcpyHostToDevice, s));
     if (c->precond == POT3D_PC_PHI_LINE) {
         // z = M^-1 r of the new FP32 residual, with r.z and r.r
-        HIP_TRY(c, launch_line<float>(c->grid_o, c->r32, c->z32, c->partial, c->line_blocks, c->sc32, 1, s));
+        HIP_TRY(c, launch_line<float>(c->grid_o, c->r32, c->z32, c->partial, c->line_blocks, s));
         HIP_TRY(c, launch_finish(resume ? kFinResume : kFinInner, c->sc32, c->partial, c->line_blocks, s));
         return POT3D_OK;
     }
@@ -843,12 +826,12 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
         const bool sweep = !line && one_sweep(c);
         const bool chip = sweep && c->oc.m > 0;
         rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev,
-                                 chip ? kInnerOnchip : (sweep ? kInnerSweeps : kInnerTwoPass));
+                                 line ? kInnerLine : chip ? kInnerOnchip : (sweep ? kInnerSweeps : kInnerTwoPass));
         if (rc != POT3D_OK) return rc;
         scale_prev = out.scale;
         if (chip) rc = run_onchip(c, s, &launches, &inner);
         else rc = replay_until_done(c, line ? c->graph32l : (sweep ? c->graph32s : c->graph32), c->sc32, s, maxit - total,
-                               sweep ? 2 * c->graph_m : c->graph_m, &launches, &inner);
+                               sweep || line ? 2 * c->graph_m : c->graph_m, &launches, &inner);
         if (rc != POT3D_OK) return rc;
         if (!chip) HIP_TRY(c, launch_x_catchup<float>(c->e32, c->sc32, c->nr, c->nt, c->np, c->pitch, s));
         total += inner.k;
@@ -1250,9 +1233,9 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     // (serving slots iterate inside the server's batched graph instead).
     int gc = serving ? POT3D_OK : capture_iterations<double>(c, c->r, c->p[0], c->p[1], c->x, c->sc, &c->graph);
     if (gc == POT3D_OK && sweep_capable(c) && precision == POT3D_FP64 && !serving)
-        gc = capture_sweeps<double>(c, c->r, c->p[0], c->p[1], c->x, c->sc, &c->graph_s);
+        gc = capture_sweeps<double>(c, c->r, c->p[0], c->p[1], c->x, c->sc, false, &c->graph_s);
     if (gc == POT3D_OK && sweep_capable(c) && precision == POT3D_FP32_REFINED && !serving)
-        gc = capture_sweeps<float>(c, c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, &c->graph32s);
+        gc = capture_sweeps<float>(c, c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, false, &c->graph32s);
     if (gc == POT3D_OK && precision == POT3D_FP32_REFINED && !serving)
         gc = capture_iterations<float>(c, c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, &c->graph32);
     if (gc != POT3D_OK) {
@@ -1373,7 +1356,7 @@ int pot3d_precondition_device(pot3d_ctx *ctx, const double *d_r, double *d_z, vo
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
     if (ctx->precond == POT3D_PC_PHI_LINE)
-        HIP_TRY(ctx, launch_line<double>(ctx->grid_a, d_r, d_z, ctx->partial, ctx->line_blocks, ctx->sc, 1, s));
+        HIP_TRY(ctx, launch_line<double>(ctx->grid_a, d_r, d_z, ctx->partial, ctx->line_blocks, s));
     else
         HIP_TRY(ctx, launch_jacobi(ctx->grid_a, d_r, d_z, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
@@ -1503,13 +1486,14 @@ int pot3d_set_preconditioner(pot3d_ctx *ctx, int pc)
     const long long rows = (long long)ctx->nr * ctx->nt;
     // one wave of resident workgroups, each wavefront walking rows with the
     // grid's stride (wider grids measured slower at 151 x 301 x 601)
-    const int per_cu = ctx->precision == POT3D_FP64 ? line_blocks_per_cu<double>(ctx->np)
-                                                    : line_blocks_per_cu<float>(ctx->np);
+    const bool fp64 = ctx->precision == POT3D_FP64;
+    const int per_cu = fp64 ? line_blocks_per_cu<double>(ctx->np, false) : line_blocks_per_cu<float>(ctx->np, false);
     ctx->line_blocks = (int)std::max<long long>(
         1, std::min<long long>({(rows + kWaves - 1) / kWaves, (long long)ctx->max_blocks,
                                 (long long)std::max(1, per_cu) * ctx->num_cu}));
     if (const int lb = env_int("POT3D_LINE_BLOCKS", 0); lb > 0)   // launch-width experiments
         ctx->line_blocks = std::min(lb, ctx->line_blocks);
+    choose_line_grid(ctx, fp64 ? line_blocks_per_cu<double>(ctx->np, true) : line_blocks_per_cu<float>(ctx->np, true));
     if (ctx->precision == POT3D_FP64) {
         if (!ctx->z) {
             HIP_TRY(ctx, dalloc(&ctx->z, (size_t)ctx->npad));
@@ -1517,8 +1501,8 @@ int pot3d_set_preconditioner(pot3d_ctx *ctx, int pc)
             HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         }
         if (!ctx->graph_l) {
-            const int rc = capture_line_iterations<double>(ctx, ctx->r, ctx->p[0], ctx->p[1], ctx->x, ctx->z, ctx->sc,
-                                                           &ctx->graph_l);
+            const int rc = capture_sweeps<double>(ctx, ctx->z, ctx->p[0], ctx->p[1], ctx->x, ctx->sc, true,
+                                                  &ctx->graph_l);
             if (rc != POT3D_OK) return rc;
         }
     } else {
@@ -1529,8 +1513,8 @@ int pot3d_set_preconditioner(pot3d_ctx *ctx, int pc)
             HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         }
         if (!ctx->graph32l) {
-            const int rc = capture_line_iterations<float>(ctx, ctx->r32, ctx->p32[0], ctx->p32[1], ctx->e32, ctx->z32,
-                                                          ctx->sc32, &ctx->graph32l);
+            const int rc = capture_sweeps<float>(ctx, ctx->z32, ctx->p32[0], ctx->p32[1], ctx->e32, ctx->sc32, true,
+                                                 &ctx->graph32l);
             if (rc != POT3D_OK) return rc;
         }
     }

@@ -85,6 +85,7 @@ struct pot3d_ctx {
     double *z = nullptr;          // phi-line: z = M^-1 r
     float *z32 = nullptr;         // ... of the FP32 inner iterations (refined mode)
     int line_blocks = 0;          // workgroups of a line pass
+    GridArgs grid_l{};            // launch of the phi-line iteration
     hipGraphExec_t graph_l = nullptr, graph32l = nullptr;
 
     bool serving = false;         // a batching-server slot: iterates in the server's graph, captures none
@@ -166,7 +167,7 @@ int start_fp64(pot3d_ctx *c, hipStream_t s, double tol, int maxit, bool sweeps);
 // Refined: r = b - A x in FP64 and the outer test; waits, then *out holds the scalars.
 int refined_outer_check(pot3d_ctx *c, hipStream_t s, DevScalars *out);
 // What runs the FP32 inner iterations: two passes (or the phi-line form), sweeps, or the on-chip kernel.
-enum InnerForm { kInnerTwoPass, kInnerSweeps, kInnerOnchip };
+enum InnerForm { kInnerTwoPass, kInnerSweeps, kInnerOnchip, kInnerLine };
 // Refined: normalised FP32 residual, e = 0, and the inner PCG start (a
 // restart, or in reliable-update mode the continuation of the previous
 // segment `prev`, which ran in normalisation scale_prev).  outer: the scalars

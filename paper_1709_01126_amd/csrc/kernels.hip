@@ -35,35 +35,6 @@
 
 namespace pot3d {
 
-// Streaming accesses: vectors that a pass reads or writes once per cell use
-// the non-temporal policy, so they do not displace the lines that are read
-// again soon (the operand's halo rows and layers, and the tiles the next pass
-// starts on).  Measured: 393 -> 369 us per FP64 iteration at 151 x 301 x 601,
-// 3.72 -> 3.48 ms at 301 x 641 x 1281, FP32-refined solve 1.28 -> 1.23 s.
-template <typename P>
-__device__ __forceinline__ auto stream_load(P p)
-{
-    return __builtin_nontemporal_load(p);
-}
-template <typename P, typename T>
-__device__ __forceinline__ void stream_store(P p, T v)
-{
-    __builtin_nontemporal_store(v, p);
-}
-
-__device__ __forceinline__ RowCoef load_row(CPtr<const RowCoef> rows, long long idx)
-{
-    RowCoef r;
-    r.rm = rows[idx].rm;
-    r.rp = rows[idx].rp;
-    r.tm = rows[idx].tm;
-    r.tp = rows[idx].tp;
-    r.s = rows[idx].s;
-    r.pq = rows[idx].pq;
-    r.pad0 = r.pad1 = 0.0;
-    return r;
-}
-
 // Diagonal of A at one point (the Jacobi preconditioner).
 template <typename V>
 __device__ __forceinline__ V diag_at(const RowCoef &rc, V dph, V ihm, V ihk)
@@ -184,8 +155,7 @@ __device__ __forceinline__ void march_body(const GridArgs &g, const StencilVecs<
     // loaded value.  Masked by multiplication (clamped data are finite).
     auto eval = [&](V a, V bold, const RowCoef &rc, V pdph, V pihm, V pihk, V mask) -> V {
         if constexpr (MODE == kUpdateP) {
-            // z = D^-1 r, or the operand itself when it is z already (block preconditioner)
-            const V z = v.zin ? a : a / diag_at<V>(rc, pdph + (V(1) - mask), pihm, pihk);
+            const V z = a / diag_at<V>(rc, pdph + (V(1) - mask), pihm, pihk);
             return vfma<V>(beta, bold, z) * mask;
         } else {
             return a * mask;
@@ -305,11 +275,9 @@ __device__ __forceinline__ void march_body(const GridArgs &g, const StencilVecs<
                     if constexpr (MODE == kUpdateR) stream_store(gout2 + idx, vfma<V>(alpha, pc, xv[m]));
                     if constexpr (MODE == kUpdateRPair)
                         stream_store(gout2 + idx, vfma<V>(alpha, pc, vfma<V>(alpha_p, pv[m], xv[m])));
-                    if (!v.zin) {   // with a block preconditioner the line pass takes r.z and r.r
-                        const V z = rn / diag_at<V>(r_, dph, ihm, ihk);
-                        acc0 += (double)rn * (double)z;
-                        acc1 += (double)rn * (double)rn;
-                    }
+                    const V z = rn / diag_at<V>(r_, dph, ihm, ihk);
+                    acc0 += (double)rn * (double)z;
+                    acc1 += (double)rn * (double)rn;
                 }
             }
         }
@@ -521,8 +489,8 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
         auto eval_row = [&](const Raw &q, const RowCoef &rc, bool on, V &a0, V &a1) {
             V e0, e1;
             if constexpr (MODE == kUpdateP) {
-                const V z0 = v.zin ? q.a.x : q.a.x / diag_at<V>(rc, dph0 + (V)(!v0), ihm0, ihk0);
-                const V z1 = v.zin ? q.a.y : q.a.y / diag_at<V>(rc, dph1 + (V)(!v1), ihm1, ihk1);
+                const V z0 = q.a.x / diag_at<V>(rc, dph0 + (V)(!v0), ihm0, ihk0);
+                const V z1 = q.a.y / diag_at<V>(rc, dph1 + (V)(!v1), ihm1, ihk1);
                 e0 = vfma<V>(beta, q.b.x, z0);
                 e1 = vfma<V>(beta, q.b.y, z1);
             } else {
@@ -549,7 +517,7 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
         };
         auto eval_cell = [&](const RawCell &q, const RowCoef &rc, V cdph, V cihm, V cihk) -> V {
             if constexpr (MODE == kUpdateP)
-                return vfma<V>(beta, q.b, v.zin ? q.a : q.a / diag_at<V>(rc, cdph, cihm, cihk));
+                return vfma<V>(beta, q.b, q.a / diag_at<V>(rc, cdph, cihm, cihk));
             else return q.a;
         };
         auto store2 = [&](GPtr<V> dst, int ip, int j, V a0, V a1) {
@@ -692,11 +660,9 @@ __device__ __forceinline__ void wave_body(const GridArgs &g, const StencilVecs<V
                     for (int e = 0; e < 2; ++e) {
                         rn[e] = ve[e] ? vfma<V>(-alpha, ap[e], rr[e]) : V(0);
                         xn[e] = ve[e] ? vfma<V>(alpha, cc[e], xx[e]) : V(0);
-                        if (!v.zin) {   // with a block preconditioner the line pass takes the sums
-                            const V z = rn[e] / diag_at<V>(r_, dph[e] + (V)(!ve[e]), ihm[e], ihk[e]);
-                            acc0 += wrow * ((double)rn[e] * (double)z);
-                            acc1 += wrow * ((double)rn[e] * (double)rn[e]);
-                        }
+                        const V z = rn[e] / diag_at<V>(r_, dph[e] + (V)(!ve[e]), ihm[e], ihk[e]);
+                        acc0 += wrow * ((double)rn[e] * (double)z);
+                        acc1 += wrow * ((double)rn[e] * (double)rn[e]);
                     }
                     if (row_on) {
                         store2(gout, i, j, rn[0], rn[1]);
@@ -825,29 +791,6 @@ stencil_wave_batch(const BatchSlot<V> *__restrict__ slots, int nslots)
 // covers every load issued before it, so writing them in the step that loads
 // them would wait for that step's other loads too.
 // ---------------------------------------------------------------------------
-// Lane l receives lane l-1 (shr) or l+1 (shl); the lane past the wavefront's
-// end receives 0 (DPP bound control: no initialised destination needed).
-__device__ __forceinline__ double shr1(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double shl1(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ float shr1(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float shl1(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xF, 0xF, true));
-}
-
 #ifdef POT3D_CHECKED
 #define SWEEP_AT(base, boff) ((base) + CHK((boff) / sizeof(V), g.npad))
 #else
@@ -1142,14 +1085,6 @@ __device__ __forceinline__ void sweep_body(const GridArgs &g, const SweepVecs<V>
 }
 #undef SWEEP_AT
 
-// The ring buffer that sweep j uses as p_{j-off} (off = 0: the one it writes).
-template <typename V>
-__device__ __forceinline__ V *ring_at(const SweepVecs<V> &v, int sweep, int off)
-{
-    const int q = (sweep % 3 + 3 - off) % 3;
-    return q == 0 ? v.ring[0] : (q == 1 ? v.ring[1] : v.ring[2]);
-}
-
 template <int R, typename V, int XM>
 __global__ void __launch_bounds__(kThreads)
 stencil_sweep(GridArgs g, SweepVecs<V> v, const RowCoef *__restrict__ rows)
@@ -1234,7 +1169,7 @@ __device__ __forceinline__ void finish_body(int which, DevScalars *sc, const dou
     const int done = sc->done;
     double s[kMaxPartials] = {0.0, 0.0, 0.0, 0.0, 0.0};
     const int ncomp = (which == kFinSigma) ? 1
-                      : (which == kFinSweep) ? 5
+                      : (which == kFinSweep || which == kFinLine) ? 5
                       : ((which == kFinInit || which == kFinOuter) ? 3 : 2);   // kFinLineInit: 2
     block_sums(partial, nb, ncomp, s);
     if (!always && done) return;
@@ -1311,13 +1246,15 @@ __device__ __forceinline__ void finish_body(int which, DevScalars *sc, const dou
                 sc->done = 1;
             }
         }
-    } else if (which == kFinSweep) {
+    } else if (which == kFinSweep || which == kFinLine) {
         // After sweep j of the one-sweep iteration (partials: r_j.z_j, r_j.r_j,
         // p_j.w_j, z_j.w_j, w_j.D^-1 w_j).  For j > 0, r_j is the residual of
         // iteration j: convergence test.  Then alpha_j, and beta_{j+1} from the
         // predicted r_{j+1}.z_{j+1}; a prediction that rounding made
         // non-positive restarts the recurrence (beta = 0, a steepest-descent
-        // step, which the next sweep's true r.z then corrects).
+        // step, which the next sweep's true r.z then corrects).  kFinLine: the
+        // fourth sum is -beta_j p_{j-1}.w_j, to which p_j.w_j makes it z_j.w_j.
+        if (which == kFinLine) s[3] += s[2];
         const int j = sc->sweep;
         sc->sweep = j + 1;
         bool stop = false;
@@ -1431,264 +1368,6 @@ finish_batch(int which, const BatchFin *__restrict__ fins, int nslots)
     finish_body(which, fins[q].sc, fins[q].partial, fins[q].nb);
 }
 
-// ---------------------------------------------------------------------------
-// phi-line block preconditioner: z = M^-1 r, where M keeps, for every (i, j)
-// row, the diagonal of A and its two periodic azimuthal weights, and drops
-// every coupling between rows (a stronger preconditioner than the point
-// Jacobi of Sec. 2.3: near the poles the azimuthal weights, which carry
-// 1 / sin(theta), dominate the diagonal).
-//
-// On a uniform phi grid the block of row (i, j) is the circulant
-//     d I - w (S + S^-1),   w = pq / dphi,   d = dphi s + 2 w
-// (S: the periodic shift by one cell), which factors as
-//     (w / mu) (I - mu S) (I - mu S^-1),   mu + 1/mu = d / w,  0 < mu < 1.
-// So z = (mu / w) v with two first-order periodic recurrences
-//     u_k = r_k + mu u_{k-1},     v_k = u_k + mu v_{k+1}        (k mod np).
-// With d / (2 w) = 1 + e, mu = 1 / (1 + e + sqrt(e (2 + e))), free of
-// cancellation for small e (pole rows) and large e alike.
-//
-// One wavefront solves one row.  Lane l owns the run of cells
-// [l NB, l NB + n_l), n_l = min(NB, max(0, np - l NB)): the row moves through
-// LDS from the coalesced layout (cell 64 q + lane) to these runs and back.
-// Each recurrence runs within a lane's run from a zero start, then an
-// inclusive scan across the 64 lanes joins the runs: a run is the affine map
-// c -> mu^n_l c + E_l (E_l its end value from a zero start), and maps compose
-// as (M1, E1) then (M2, E2) = (M1 M2, E1 M2 + E2).  The carry into run l then
-// enters its cell t with mu^(t + 1) (forward; mu^(n_l - t) backward).  The
-// periodic wrap is closed afterwards: the value that comes round the row is
-// the non-periodic end value divided by 1 - mu^np, and it enters every cell
-// with its own power of mu (the scan's products give mu^(l NB) and
-// mu^(np - (l + 1) NB)).  Every value is FP64; each row reads r once and
-// writes z once (16 bytes per unknown in FP64 storage).  Per-workgroup
-// partial sums of r.z and r.r follow in fixed order.
-// ---------------------------------------------------------------------------
-// m^e for an integer e >= 0 by binary powering.
-__device__ __forceinline__ double powi(double m, int e)
-{
-    double r = 1.0;
-    while (e > 0) {
-        if (e & 1) r *= m;
-        m *= m;
-        e >>= 1;
-    }
-    return r;
-}
-
-// Inclusive scans of affine maps c -> M c + E across the 64 lanes, without
-// LDS: DPP shifts by 1, 2, 4, 8 inside each 16-lane row, then the rows are
-// chained through their composites read out of one lane each.  UP: lane l
-// ends with the composite of lanes 0..l applied in order, (M1, E1) then
-// (M2, E2) = (M1 M2, E1 M2 + E2).  Down: the composite of lanes l..63 with
-// the lanes to the right applied first, (M, F) of l then the rest R =
-// (M Mr, F + M Fr).
-template <bool UP>
-__device__ __forceinline__ void affine_scan(double &M, double &E, int lane)
-{
-    // Branch-free: a DPP read of a lane that is switched off returns 0, so the
-    // shifts must run with every lane on.  A source outside the row reads
-    // (0, 0), which the step turns into the identity (1, 0) by adding 1 to M.
-    const int rl = lane & 15, row = lane >> 4;
-    auto step = [&](double Mo, double Eo, bool ok) {
-        E = __builtin_fma(Eo, M, E);
-        M = (Mo + (ok ? 0.0 : 1.0)) * M;
-    };
-    if (UP) {
-        { const double Mo = row_shift<0x111>(M), Eo = row_shift<0x111>(E); step(Mo, Eo, rl >= 1); }
-        { const double Mo = row_shift<0x112>(M), Eo = row_shift<0x112>(E); step(Mo, Eo, rl >= 2); }
-        { const double Mo = row_shift<0x114>(M), Eo = row_shift<0x114>(E); step(Mo, Eo, rl >= 4); }
-        { const double Mo = row_shift<0x118>(M), Eo = row_shift<0x118>(E); step(Mo, Eo, rl >= 8); }
-        // rows: prefix composites of rows 0, 0-1, 0-2 from lanes 15, 31, 47
-        const double m0 = lane_value(M, 15), e0 = lane_value(E, 15);
-        const double m1 = lane_value(M, 31), e1 = lane_value(E, 31);
-        const double m2 = lane_value(M, 47), e2 = lane_value(E, 47);
-        const double p1m = m0 * m1, p1e = __builtin_fma(e0, m1, e1);     // rows 0-1
-        const double p2m = p1m * m2, p2e = __builtin_fma(p1e, m2, e2);   // rows 0-2
-        const double pm = row == 0 ? 1.0 : row == 1 ? m0 : row == 2 ? p1m : p2m;
-        const double pe = row == 0 ? 0.0 : row == 1 ? e0 : row == 2 ? p1e : p2e;
-        E = __builtin_fma(pe, M, E);
-        M = pm * M;
-    } else {
-        { const double Mo = row_shift<0x101>(M), Eo = row_shift<0x101>(E); step(Mo, Eo, rl + 1 < 16); }
-        { const double Mo = row_shift<0x102>(M), Eo = row_shift<0x102>(E); step(Mo, Eo, rl + 2 < 16); }
-        { const double Mo = row_shift<0x104>(M), Eo = row_shift<0x104>(E); step(Mo, Eo, rl + 4 < 16); }
-        { const double Mo = row_shift<0x108>(M), Eo = row_shift<0x108>(E); step(Mo, Eo, rl + 8 < 16); }
-        // rows: suffix composites of rows 3, 2-3, 1-3 from lanes 48, 32, 16
-        const double m3 = lane_value(M, 48), e3 = lane_value(E, 48);
-        const double m2 = lane_value(M, 32), e2 = lane_value(E, 32);
-        const double m1 = lane_value(M, 16), e1 = lane_value(E, 16);
-        const double s2m = m2 * m3, s2e = __builtin_fma(m2, e3, e2);     // rows 2-3
-        const double s1m = m1 * s2m, s1e = __builtin_fma(m1, s2e, e1);   // rows 1-3
-        const double sm = row == 3 ? 1.0 : row == 2 ? m3 : row == 1 ? s2m : s1m;
-        const double se = row == 3 ? 0.0 : row == 2 ? e3 : row == 1 ? s2e : s1e;
-        E = __builtin_fma(se, M, E);
-        M = sm * M;
-    }
-}
-
-// The value at position n - 1 of a register array (0 for n = 0), by a
-// chain of selects (the index is per lane).
-template <int NB>
-__device__ __forceinline__ double t_end(const double (&u)[NB], int n)
-{
-    double v = 0.0;
-#pragma unroll
-    for (int t = 0; t < NB; ++t) v = (t == n - 1) ? u[t] : v;
-    return v;
-}
-
-// NB = cells per lane's run, ceil(np / 64) (np in (64 (NB - 1), 64 NB]).  V is
-// the storage type of r and z (FP64, or FP32 for the inner iterations of the
-// refined mode); the recurrences always run in FP64.  LDS: one row per
-// wavefront, cell k at k + k / NB (one slot of padding per run, so that the
-// lanes' strided run accesses spread over the banks).
-template <int NB, typename V>
-__global__ void __launch_bounds__(kThreads)
-line_solve_kernel(GridArgs g, const V *__restrict__ rin, V *__restrict__ zout, double *__restrict__ partial,
-                  const DevScalars *__restrict__ sc, int ignore_done)
-{
-    const CPtr<const DevScalars> csc = to_const(sc);
-    if (!ignore_done && csc->done) return;   // uniform over the workgroup
-    constexpr int kRowSlots = NB * kWave + kWave;
-    __shared__ double rowbuf[kWaves][kRowSlots];
-    __shared__ double red[kWaves][2];
-    const GPtr<const V> gr = to_global(rin);
-    const GPtr<V> gz = to_global(zout);
-    const CPtr<const RowCoef> crows = to_const(g.rows);
-    const int np = g.np;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    double *const row = rowbuf[w];
-    const int n_l = min(NB, max(0, np - lane * NB));   // cells of this lane's run
-    const int run0 = lane * (NB + 1);                  // LDS slot of the run's first cell
-    const int last_lane = (np - 1) / NB;               // the lane that holds cell np - 1
-    const double dph = to_global(g.dphi)[0];           // uniform phi: every width is 2 pi / np
-    const double ih = to_global(g.ih)[0];
-    const long long nrows = (long long)g.nr * g.nt;
-    double acc_rz = 0.0, acc_rr = 0.0;
-
-    // r of a row, coalesced (cell 64 q + lane), into registers (storage type)
-    auto load_r = [&](long long rw, V (&rq)[NB]) {
-        const long long base = rw * g.pitch;
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int k = q * kWave + lane;
-            rq[q] = k < np ? stream_load(gr + CHK(base + k, g.npad)) : V(0);
-        }
-    };
-    // FP32 storage: the next row's r is loaded under this row's work (the
-    // registers it takes leave the occupancy unchanged there; in FP64 they
-    // would cost a wavefront per SIMD at 601 cells)
-    constexpr bool kPrefetch = sizeof(V) == 4;
-    const long long rstride = (long long)gridDim.x * kWaves;
-    V rq[NB];
-    long long rw = (long long)blockIdx.x * kWaves + w;
-    if (kPrefetch && rw < nrows) load_r(rw, rq);
-    for (; rw < nrows; rw += rstride) {
-        const RowCoef rc = load_row(crows, CHK(rw, nrows));
-        const long long base = rw * g.pitch;
-        if (!kPrefetch) load_r(rw, rq);
-        // r into LDS, then each lane's run into registers
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int k = q * kWave + lane;
-            if (k < np) row[CHK(k + k / NB, kRowSlots)] = (double)rq[q];
-        }
-        if (kPrefetch && rw + rstride < nrows) load_r(rw + rstride, rq);
-        wave_sync();
-        double rv[NB], u[NB];
-#pragma unroll
-        for (int t = 0; t < NB; ++t) rv[t] = t < n_l ? row[CHK(run0 + t, kRowSlots)] : 0.0;
-        wave_sync();
-
-        const double wgt = rc.pq * ih;                       // azimuthal weight w
-        const double e = dph * rc.s / (2.0 * wgt);           // d / (2 w) - 1 > 0
-        const double mu = 1.0 / (1.0 + e + sqrt(e * (2.0 + e)));
-        const double inv_wrap = 1.0 / (1.0 - powi(mu, np)); // 1 / (1 - mu^np)
-        const double m_run = powi(mu, n_l);                  // mu^n_l (1 for an empty run)
-
-        // forward: u_k = r_k + mu u_{k-1}; the run from a zero start
-        double acc = 0.0;
-#pragma unroll
-        for (int t = 0; t < NB; ++t) {
-            acc = __builtin_fma(mu, acc, rv[t]);
-            u[t] = acc;
-        }
-        double M = m_run, E = t_end(u, n_l);
-        affine_scan<true>(M, E, lane);
-        // carry into this run (u at cell l NB - 1, non-periodic) and mu^(l NB)
-        // (lane 0 reads 0 for both; branch-free, as in affine_scan)
-        const double C = shr1(E);
-        const double B = shr1(M) + (lane == 0 ? 1.0 : 0.0);
-        const double ulast = lane_value(E, last_lane);      // u_{np-1}, non-periodic
-        {
-            const double cin = __builtin_fma(B, ulast * inv_wrap, C);   // carry plus the wrap
-            double pw = mu;
-#pragma unroll
-            for (int t = 0; t < NB; ++t) {
-                u[t] = t < n_l ? __builtin_fma(pw, cin, u[t]) : 0.0;
-                pw *= mu;
-            }
-        }
-        // backward: v_k = u_k + mu v_{k+1}; the run from a zero end
-        acc = 0.0;
-#pragma unroll
-        for (int t = NB - 1; t >= 0; --t) {
-            acc = __builtin_fma(mu, acc, u[t]);
-            u[t] = acc;
-        }
-        M = m_run;
-        double F = u[0];
-        affine_scan<false>(M, F, lane);
-        // v at cell (l + 1) NB (non-periodic) and mu^(np - (l + 1) NB)
-        // (lane 63 reads 0 for both; branch-free)
-        const double D = shl1(F);
-        const double T = shl1(M) + (lane == kWave - 1 ? 1.0 : 0.0);
-        const double v0 = lane_value(F, 0);                 // v_0, non-periodic
-        const double scale = mu / wgt;
-        {
-            const double din = __builtin_fma(T, v0 * inv_wrap, D);   // carry plus the wrap
-            double pw = mu;
-#pragma unroll
-            for (int t = NB - 1; t >= 0; --t) {
-                if (t < n_l) {
-                    const double z = scale * __builtin_fma(pw, din, u[t]);
-                    u[t] = z;
-                    acc_rz = __builtin_fma(rv[t], z, acc_rz);
-                    acc_rr = __builtin_fma(rv[t], rv[t], acc_rr);
-                    pw *= mu;
-                }
-            }
-        }
-        // z back through LDS to the coalesced layout
-#pragma unroll
-        for (int t = 0; t < NB; ++t)
-            if (t < n_l) row[CHK(run0 + t, kRowSlots)] = u[t];
-        wave_sync();
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int k = q * kWave + lane;
-            if (k < np) stream_store(gz + CHK(base + k, g.npad), (V)row[CHK(k + k / NB, kRowSlots)]);
-        }
-        wave_sync();
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        acc_rz += __shfl_xor(acc_rz, off, kWave);
-        acc_rr += __shfl_xor(acc_rr, off, kWave);
-    }
-    if (lane == 0) {
-        red[w][0] = acc_rz;
-        red[w][1] = acc_rr;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        double t = 0.0;
-#pragma unroll
-        for (int q = 0; q < kWaves; ++q) t += red[q][threadIdx.x];
-        to_global(partial)[CHK((long long)threadIdx.x * gridDim.x + blockIdx.x, 2LL * gridDim.x)] = t;
-    }
-}
-
 // Point Jacobi, z = D^-1 r (rows of g.pitch).
 __global__ void __launch_bounds__(256)
 jacobi_kernel(GridArgs g, const double *__restrict__ r, double *__restrict__ z)
@@ -1713,53 +1392,6 @@ hipError_t launch_jacobi(const GridArgs &g, const double *r, double *z, hipStrea
     jacobi_kernel<<<(unsigned)std::min<long long>(nrows, 65536), 256, 0, s>>>(g, r, z);
     return hipGetLastError();
 }
-
-template <int NB, typename V>
-static hipError_t launch_line_nb(int nb, const GridArgs &g, const V *r, V *z, double *partial, int nblocks,
-                                 const DevScalars *sc, int ignore_done, hipStream_t s)
-{
-    if constexpr (NB > 1) {
-        if (nb < NB) return launch_line_nb<NB - 1, V>(nb, g, r, z, partial, nblocks, sc, ignore_done, s);
-    }
-    line_solve_kernel<NB, V><<<nblocks, kThreads, 0, s>>>(g, r, z, partial, sc, ignore_done);
-    return hipGetLastError();
-}
-
-template <typename V>
-hipError_t launch_line(const GridArgs &g, const V *r, V *z, double *partial, int nblocks, const DevScalars *sc,
-                       int ignore_done, hipStream_t s)
-{
-    const int nb = (g.np + kWave - 1) / kWave;
-    if (nb < 1 || nb > kMaxLineCells / kWave) return hipErrorInvalidValue;
-    return launch_line_nb<kMaxLineCells / kWave, V>(nb, g, r, z, partial, nblocks, sc, ignore_done, s);
-}
-template hipError_t launch_line<double>(const GridArgs &, const double *, double *, double *, int,
-                                        const DevScalars *, int, hipStream_t);
-template hipError_t launch_line<float>(const GridArgs &, const float *, float *, double *, int, const DevScalars *,
-                                       int, hipStream_t);
-
-template <int NB, typename V>
-static int line_blocks_per_cu_nb(int nb)
-{
-    if constexpr (NB > 1) {
-        if (nb < NB) return line_blocks_per_cu_nb<NB - 1, V>(nb);
-    }
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(&line_solve_kernel<NB, V>),
-                                                     kThreads, 0) != hipSuccess)
-        return 0;
-    return n;
-}
-
-template <typename V>
-int line_blocks_per_cu(int np)
-{
-    const int nb = (np + kWave - 1) / kWave;
-    if (nb < 1 || nb > kMaxLineCells / kWave) return 0;
-    return line_blocks_per_cu_nb<kMaxLineCells / kWave, V>(nb);
-}
-template int line_blocks_per_cu<double>(int);
-template int line_blocks_per_cu<float>(int);
 
 // ---------------------------------------------------------------------------
 // Refinement helpers (pointwise over the padded arrays; padding stays zero).
@@ -2409,7 +2041,7 @@ unsigned take_oob_line(hipStream_t s)
         const unsigned zero = 0;
         (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
     }
-    return line ? line : onchip_oob_line();
+    return line ? line : (onchip_oob_line() | line_oob_line());
 #else
     (void)s;
     return 0;

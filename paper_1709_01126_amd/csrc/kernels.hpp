@@ -15,7 +15,8 @@ enum FinWhich : int {
     kFinInner = 5,  // refinement, after the r.z pass on the FP32 residual: inner start
     kFinResume = 6, // refinement, reliable update: as kFinInner, keeping the direction
     kFinSweep = 7,  // one-sweep iteration: convergence test, alpha, predicted r.z, beta
-    kFinLineInit = 8  // block preconditioner, after the first line pass: rho = r.z
+    kFinLineInit = 8, // block preconditioner, after the first line pass: rho = r.z
+    kFinLine = 9      // block preconditioner, after the two kernels of an iteration: as kFinSweep
 };
 
 // Partial sums per workgroup that a finisher may read (the one-sweep kernel
@@ -90,11 +91,16 @@ hipError_t launch_gauge(double *x, const double *vr, const double *vt, const dou
 // [0][b] = r.z and [1][b] = r.r for b < nblocks.
 constexpr int kMaxLineCells = 32 * 64;
 template <typename V>
-hipError_t launch_line(const GridArgs &g, const V *r, V *z, double *partial, int nblocks, const DevScalars *sc,
-                       int ignore_done, hipStream_t s);
-// Workgroups of the line pass resident per CU (0 if unknown).
+hipError_t launch_line(const GridArgs &g, const V *r, V *z, double *partial, int nblocks, hipStream_t s);
+// One iteration with it, in the buffers of the one-sweep form (the ring's
+// z_0 = M^-1 r_0): partials [5][nblocks] for kFinLine.  g: chunks of ci layers,
+// ntj groups of kWaves polar rows, nblocks workgroups that share them.
 template <typename V>
-int line_blocks_per_cu(int np);
+hipError_t launch_line_iteration(const GridArgs &g, const SweepVecs<V> &v, hipStream_t s);
+unsigned line_oob_line();   // checked builds, as take_oob_line
+// Workgroups of the line pass, or of the line iteration, resident per CU (0 if unknown).
+template <typename V>
+int line_blocks_per_cu(int np, bool iteration);
 
 // Point Jacobi z = D^-1 r (padded layout).
 hipError_t launch_jacobi(const GridArgs &g, const double *r, double *z, hipStream_t s);
