@@ -36,7 +36,7 @@ HBM_PEAK_GBS = 8000.0
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for name in ("kernels.hip", "solver.hpp"):
+    for name in ("kernels.hip", "stencil_ops.hpp", "solver.hpp"):
         with open(os.path.join(ROOT, "paper_1709_01126_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -61,18 +61,29 @@ def load_traffic(workload: str, kernel: str):
 # algorithmic bytes per unknown of each iteration kernel, and the kernel-name
 # fragments that identify it in a trace
 # fragments that identify it in a trace.  One-sweep form: the even sweeps
-# leave x to the odd ones (32 N: read r, p_old; write r, p), the odd sweeps
-# update x for both (48 N: also read and write x); "sweep" is the sweep that
+# leave x to the odd ones (24 N: read the last two directions, write the new
+# one), the odd sweeps update x for both (40 N: also read and write x); "sweep" is the sweep that
 # updates x every time (POT3D_SWEEP_X=1).
-KERNEL_KEYS = {"sweep_even": (32.0, ("stencil_sweep<", "double, 1>")),
-               "sweep_odd": (48.0, ("stencil_sweep<", "double, 2>")),
-               "sweep": (48.0, ("stencil_sweep<", "double, 0>")),
+KERNEL_KEYS = {"sweep_even": (24.0, ("stencil_sweep<", "double, 1>")),
+               "sweep_odd": (40.0, ("stencil_sweep<", "double, 2>")),
+               "sweep": (40.0, ("stencil_sweep<", "double, 0>")),
                "update_p": (24.0, (", 2, double>",)), "update_r": (40.0, (", 3, double>",)),
-               # the r/x update of the two-pass and phi-line iterations, x once per pair
+               # the r/x update of the two-pass iteration, x once per pair
                "update_r_skip": (24.0, (", 4, double>",)), "update_r_pair": (48.0, (", 5, double>",)),
-               "sweep_fp32_even": (16.0, ("stencil_sweep<", "float, 1>")),
-               "sweep_fp32_odd": (24.0, ("stencil_sweep<", "float, 2>")),
-               "line": (16.0, ("line_solve_kernel<",))}
+               "sweep_fp32_even": (12.0, ("stencil_sweep<", "float, 1>")),
+               "sweep_fp32_odd": (20.0, ("stencil_sweep<", "float, 2>")),
+               "line": (16.0, ("line_solve_kernel<",)),
+               # the phi-line iteration: step (the mean of 24 N and, with x, 40 N) and curvature
+               "line_step": (32.0, ("line_iteration_kernel<", "double, true>")),
+               "line_curvature": (8.0, ("line_iteration_kernel<", "double, false>"))}
+
+
+def moved_bytes(stats, n: int) -> float:
+    """HBM bytes that the FP64 kernels have to move per iteration.  pot3d_stats
+    reports reference bytes, with r, p (and z) read and written; the one-sweep
+    and phi-line forms carry the last two directions instead."""
+    per = round(stats["bytes_per_iter"] / n)
+    return n * float({40: 32, 48: 40, 76: 40, 80: 48}.get(per, per))
 
 
 def summarize_pmc(workload: str, fetch_dir: str, write_dir: str):
@@ -612,11 +623,11 @@ def main():
     del fbr, fbt, fbp
     it_per_s = total_iters / elapsed
     one_sweep = stats["iteration"] == pot3d.ITER_ONE_SWEEP
-    bytes_iter = stats["bytes_per_iter"]
+    bytes_iter = moved_bytes(stats, w.n)
     # per-kernel average launch time as the kernels run in a solve
     # (device wall-clock stamps per launch inside a replayed graph)
     ms_a, ms_b = solver.time_kernels(args.kernel_reps)
-    paired = one_sweep and abs(bytes_iter - 40.0 * w.n) < 0.5
+    paired = one_sweep and abs(bytes_iter - 32.0 * w.n) < 0.5
     if paired:
         kern = {"sweep_even": {"alg_bytes_per_launch": KERNEL_KEYS["sweep_even"][0] * w.n, "ms": ms_a},
                 "sweep_odd": {"alg_bytes_per_launch": KERNEL_KEYS["sweep_odd"][0] * w.n, "ms": ms_b}}
@@ -632,19 +643,19 @@ def main():
         v["gbs"] = v["alg_bytes_per_launch"] / (v["ms"] * 1e-3) / 1e9
     if paired:
         # the sweeps run in pairs (even, odd) that alternate through the solve:
-        # the pair is the unit, 80 N bytes over the two launch times, quoted per
-        # launch (40 N over their mean)
+        # the pair is the unit, 64 N bytes over the two launch times, quoted per
+        # launch (32 N over their mean)
         ev, od = kern["sweep_even"], kern["sweep_odd"]
         ms_mean = 0.5 * (ev["ms"] + od["ms"])
-        gbs = 40.0 * w.n / (ms_mean * 1e-3) / 1e9
+        gbs = 32.0 * w.n / (ms_mean * 1e-3) / 1e9
         t_ev, t_od = load_traffic(w.name, "sweep_even"), load_traffic(w.name, "sweep_odd")
         traffic = None if t_ev is None or t_od is None else 0.5 * (t_ev + t_od)
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                     "kernel": f"{kernel_name(stats, 'sweep_even')} + {kernel_name(stats, 'sweep_odd')}",
-                    "alg_bytes_per_launch": 40.0 * w.n, "ms_per_launch": ms_mean,
-                    "basis": "40 N bytes per launch, the mean of an even sweep (32 N: read r, p_old; write r, p) "
-                             "and an odd one (48 N: also read and write x, for both sweeps)"}
+                    "alg_bytes_per_launch": 32.0 * w.n, "ms_per_launch": ms_mean,
+                    "basis": "32 N bytes per launch, the mean of an even sweep (24 N: read the last two directions, write "
+                             "the new one) and an odd one (40 N: also read and write x, for both sweeps)"}
     else:
         dom = max(kern, key=lambda k: kern[k]["ms"])
         ms_mean = kern[dom]["ms"]
@@ -657,7 +668,7 @@ def main():
         # the same launch time on the textbook two-pass basis of one PCG
         # iteration (64 N: read r, p, x and re-read p, r; write p, x, r), which
         # is what an iteration costs without the one-sweep rearrangement, and
-        # on the sweep that updates x every time (48 N)
+        # on a sweep that reads and writes r, p and x every time (48 N)
         roofline["achieved_64N_basis"] = round(64.0 * w.n / (ms_mean * 1e-3) / 1e9, 1)
         roofline["frac_64N_basis"] = round(roofline["achieved_64N_basis"] / HBM_PEAK_GBS, 4)
         roofline["achieved_48N_basis"] = round(48.0 * w.n / (ms_mean * 1e-3) / 1e9, 1)
@@ -724,8 +735,8 @@ def main():
         del d_phi_cw
     if not args.no_line:
         # the phi-line block preconditioner on the same grid and data: fewer
-        # iterations, 76 N bytes each on average (direction update on z, r/x
-        # update with x once per pair, line pass)
+        # iterations, 40 N bytes each on average (step 24 N, or 40 N with x once
+        # per pair; curvature 8 N)
         solver.set_preconditioner(pot3d.PC_PHI_LINE)
         d_phi_l = torch.empty_like(d_phi)
         stl, itl, rrl = solver.solve_device(d_br, d_phi_l, w.tol, maxit)
@@ -740,8 +751,8 @@ def main():
             "solve_s": round(tl, 4), "speedup_vs_point_jacobi": round(result["fp64_solve_s"] / tl, 3),
             "iters": itl, "iters_point_jacobi": result["config"]["iters_per_solve"],
             "iters_per_s": round(itl / tl, 2), "loop_us_per_iter": round(sl["loop_ms"] * 1e3 / max(1, itl), 2),
-            "bytes_per_unknown": round(sl["bytes_per_iter"] / w.n, 3),
-            "gbs_alg": round(sl["bytes_per_iter"] * itl / (sl["loop_ms"] * 1e-3) / 1e9, 1),
+            "bytes_per_unknown": round(moved_bytes(sl, w.n) / w.n, 3),
+            "gbs_alg": round(moved_bytes(sl, w.n) * itl / (sl["loop_ms"] * 1e-3) / 1e9, 1),
             "status": pot3d.STATUS_NAMES.get(stl, stl), "relres_true": rrl,
             "max_rel_err_vs_oracle_samples": err_vs_samples(torch, d_phi_l, golden_samples(w.name + "_phi_line")),
             "max_rel_diff_vs_point_jacobi": float(torch.max(torch.abs(d_phi_l - d_phi)).item()
@@ -861,11 +872,11 @@ def large_grid_leg(torch, dev, name):
     loop_us = stats["loop_ms"] * 1e3 / max(1, it)
     out = {"workload": w.describe(), "data": "dipole 5 cos(theta)", "n": w.n, "fixed_iters": it, "loop_us_per_iter": round(loop_us, 2),
            "iters_per_s": round(1e6 / loop_us, 2),
-           "gbs_alg_per_iteration": round(stats["bytes_per_iter"] / (loop_us * 1e-6) / 1e9, 1),
+           "gbs_alg_per_iteration": round(moved_bytes(stats, w.n) / (loop_us * 1e-6) / 1e9, 1),
            "sweep_ms_even_odd": [round(ms_e, 4), round(ms_o, 4)], "sweep_ms_mean": round(ms_sweep, 4),
            "sweep_traffic_even_odd": [load_traffic(w.name, "sweep_even"), load_traffic(w.name, "sweep_odd")],
-           "sweep_gbs_alg": round(stats["bytes_per_iter"] / (ms_sweep * 1e-3) / 1e9, 1),
-           "sweep_frac": round(stats["bytes_per_iter"] / (ms_sweep * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+           "sweep_gbs_alg": round(moved_bytes(stats, w.n) / (ms_sweep * 1e-3) / 1e9, 1),
+           "sweep_frac": round(moved_bytes(stats, w.n) / (ms_sweep * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
            "launch": {k2: stats[k2] for k2 in ("sweep_rows", "chunk_s", "blocks_s", "pitch")}}
     print(f"[bench] large grid: {json.dumps(out)}", file=sys.stderr, flush=True)
     return out

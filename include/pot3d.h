@@ -136,7 +136,8 @@ typedef struct pot3d_stats {
     int sweep_rows;          /* one-sweep kernel: tile box rows per wavefront (4, 6 or 8)   */
     int chunk_s, blocks_s;   /* one-sweep kernel: radial layers per chunk, workgroups      */
     int precond;             /* POT3D_PC_* of the last solve                               */
-    int blocks_l;            /* workgroups of the phi-line pass (0 unless POT3D_PC_PHI_LINE)*/
+    int blocks_l;            /* workgroups of the pass z = M^-1 r at a solve's start (0 unless
+                                POT3D_PC_PHI_LINE)                                         */
 } pot3d_stats;
 
 /*
@@ -293,14 +294,14 @@ int pot3d_set_iteration(pot3d_ctx *ctx, int iteration);
  * uses point Jacobi; Sec. 6 asks for stronger ones that still suit vector
  * hardware):
  *   POT3D_PC_JACOBI    point Jacobi (default), either iteration form;
- *   POT3D_PC_PHI_LINE  phi-line blocks.  Each PCG iteration then runs the
- *                      direction update on z = M^-1 r, the r/x update, and a
- *                      line pass that solves the rows (one wavefront per row:
- *                      the circulant block of a uniform phi grid factors
- *                      into two first-order periodic recurrences, always
- *                      evaluated in FP64) and writes z: 76 bytes per unknown
- *                      per FP64 iteration (38 per FP32 one) against 40 or 60
- *                      for point Jacobi, for fewer iterations.  Allocates one
+ *   POT3D_PC_PHI_LINE  phi-line blocks.  Each PCG iteration then runs two
+ *                      kernels, a step and a curvature, one wavefront per
+ *                      (r, theta) row (the circulant block of a uniform phi
+ *                      grid factors into two first-order periodic
+ *                      recurrences, always evaluated in FP64); they move 40
+ *                      bytes per unknown per FP64 iteration (20 per FP32 one)
+ *                      against 32 or 60 for point Jacobi, for fewer
+ *                      iterations.  Allocates one
  *                      more vector (8 N or 4 N bytes) on first use.
  * POT3D_EINVAL (nothing changed) unless the context's phi faces are uniform
  * (every width 2 pi / np to 1e-12 relative) with np <= 2048, or for another

@@ -3,11 +3,13 @@
 // A context owns, on one device:
 //   * the separable metric tables of the Sec. 2.2 operator (per (i, j) row
 //     and per k);
-//   * the PCG vectors x, r, p (two buffers, alternating) in a padded
-//     phi-fastest layout;
+//   * the PCG vectors x, r, p (two buffers, alternating; in the one-sweep form
+//     r's buffer and the two are a ring of directions) in a padded phi-fastest
+//     layout;
 //   * the right-hand-side layer, the per-workgroup partial sums and the
 //     scalar state;
-//   * a HIP graph of m PCG iterations.
+//   * a HIP graph of m PCG iterations, and for small grids the tables and
+//     exchange buffers of the on-chip kernel, which takes the graph's place.
 // A solve copies Br in, builds b and the initial residual, replays the graph
 // until the device sets its done flag, then recomputes the true residual and
 // the pole values (eq. (3)) and copies Phi out.  There is one host<->device
@@ -289,7 +291,7 @@ int resident_blocks(const pot3d_ctx *c, int mode, int tile)
 // no tail.  The FP64 r/x update, whose x update comes once per pair of
 // iterations, runs on the four-row wavefront kernel with about 4096
 // workgroups: two-pass solve 1.906 s against 2.025 s on 8-row LDS-plane
-// tiles, phi-line solve 0.966 s against 0.998 s.
+// tiles.
 // FP32 passes move half the bytes per cell, so a workgroup keeps fewer bytes
 // in flight and more are needed: the p update about 6 per CU, the r/x update
 // on the two-row wavefront kernel with about 4096 workgroups.  (The 8-row

@@ -80,11 +80,12 @@ struct pot3d_ctx {
 
     // Preconditioner of single solves (the FP64 iterations, or the FP32 inner
     // ones of the refined mode): point Jacobi (PC1) or the phi-line blocks,
-    // which iterate in two passes plus a line pass that writes z.
+    // which iterate in two kernels (a step and a curvature) in the same ring,
+    // with z's buffer in the place of r's.
     int precond = POT3D_PC_JACOBI;
-    double *z = nullptr;          // phi-line: z = M^-1 r
+    double *z = nullptr;          // phi-line: z_0 = M^-1 r_0, then a direction of the ring
     float *z32 = nullptr;         // ... of the FP32 inner iterations (refined mode)
-    int line_blocks = 0;          // workgroups of a line pass
+    int line_blocks = 0;          // workgroups of the pass z = M^-1 r
     GridArgs grid_l{};            // launch of the phi-line iteration
     hipGraphExec_t graph_l = nullptr, graph32l = nullptr;
 

@@ -23,7 +23,9 @@
 //      and two finishers; the form is fixed when the server is created).
 //      Each kernel of it covers every active slot (a slot table in device
 //      memory maps workgroups to slots), and slots that have converged are
-//      masked by their own done flags.
+//      masked by their own done flags.  A slot whose grid the on-chip kernel
+//      fits takes no part in the batch: it advances by a bounded number of
+//      iterations in that kernel, after the replay, one slot after the other.
 // A step queues its replay before it reads the statuses of the previous one,
 // so in steps where no solve ends or starts the device has the next replay
 // queued while the host decides.  A step that retires or admits a request
