@@ -196,10 +196,29 @@ GridArgs make_grid(const pot3d_ctx *c, int tile, int target, int ci_fixed)
     return g;
 }
 
+bool streams_from_hbm(const pot3d_ctx *c);
+
+// Azimuthal cells of a sweep's tile.  A box is 64 lanes wide whatever its
+// tile, so the work goes with the number of tiles in a row; 56-cell tiles are
+// taken where they are fewer by an eighth, and the vectors don't stream from
+// HBM, where the halves of lines cost more than that.  Mean of the even and
+// odd sweep with 48 / 56 cells, us (FP64; FP32): 70 x 140 x 280 40.4 / 39.2;
+// 37.3 / 34.8, 90 x 180 x 360 62.9 / 56.4; 46.5 / 45.8, 120 x 241 x 481
+// 110.6 / 94.2; 82.3 / 75.2, 140 x 280 x 560 174.1 / 151.5; 107.7 / 100.0,
+// 151 x 301 x 601 205.7 / 203.4; 123.9 / 123.2, 180 x 361 x 721 412.7 / 412.9;
+// 241.7 / 223.4.  Where they save less: 101 x 201 x 401 68.3 / 68.6; 53.8 /
+// 54.3, 128 x 256 x 512 120.9 / 122.6; 85.8 / 88.3, 200 x 400 x 800 479.2 /
+// 484.5; 291.2 / 293.6.  From HBM: 301 x 641 x 1281 1880 / 1963 per iteration.
+int sweep_tk(const pot3d_ctx *c)
+{
+    const int n48 = (c->np + 47) / 48, n56 = (c->np + 55) / 56;
+    return (8 * n56 <= 7 * n48 && !streams_from_hbm(c)) ? 56 : 48;
+}
+
 // Launch shape of the one-sweep kernel (`rows` box rows per wavefront):
-// tiles of tj x tk interior cells (tj <= 4 rows - 4; tk = 48 cells by
-// default, a multiple of 16 so that a tile's stores cover whole 128-byte
-// lines) over radial chunks of ci layers.  Every workgroup walks its chunk
+// tiles of tj x tk interior cells (tj <= 4 rows - 4; tk = 48 cells, a multiple
+// of 16 so that a tile's stores cover whole 128-byte lines, or 56, whose stores
+// cover whole 64-byte halves; sweep_tk) over radial chunks of ci layers.  Every workgroup walks its chunk
 // from start to end, so the launch runs fastest as a single wave of
 // workgroups that fills as many of the `target` resident slots as possible:
 // the rule takes the tile height (FP64: down to 4 rows below the maximum;
@@ -213,10 +232,10 @@ GridArgs make_grid(const pot3d_ctx *c, int tile, int target, int ci_fixed)
 // against 194 us for 10-row tiles (1209).  A grid with more tiles than slots
 // takes the tallest tiles and whole-radius chunks.  POT3D_SWEEP_TJ,
 // POT3D_SWEEP_TK and POT3D_SWEEP_CI override.
-GridArgs make_sweep_grid(const pot3d_ctx *c, int rows, int target)
+GridArgs make_sweep_grid(const pot3d_ctx *c, int rows, int target, bool widen)
 {
     const int tjmax = 4 * rows - 4;
-    const int tk = std::max(1, std::min(60, env_int("POT3D_SWEEP_TK", 48)));
+    const int tk = std::max(1, std::min(60, env_int("POT3D_SWEEP_TK", widen ? sweep_tk(c) : 48)));
     const int ntk = (c->np + tk - 1) / tk;
     const int tj_env = std::min(tjmax, env_int("POT3D_SWEEP_TJ", 0));
     const int ci_env = env_int("POT3D_SWEEP_CI", 0);
@@ -380,7 +399,7 @@ void choose_launch(pot3d_ctx *c)
         const int ts = env_int("POT3D_TARGET_BLOCKS_S", 0);
         const int per_cu = fp32 ? sweep_blocks_per_cu<float>(c->sweep_rows) : sweep_blocks_per_cu<double>(c->sweep_rows);
         const int resident = std::max(1, per_cu) * std::max(1, c->num_cu);
-        c->grid_s = make_sweep_grid(c, c->sweep_rows, ts > 0 ? ts : resident);
+        c->grid_s = make_sweep_grid(c, c->sweep_rows, ts > 0 ? ts : resident, true);
         c->grid_s.reverse = env_int("POT3D_REVERSE_S", 0) != 0;
         c->max_blocks = std::max(c->max_blocks, c->grid_s.nblocks);
     }

@@ -142,7 +142,8 @@ void fill_tables(int nr, int nt, int np, const double *rf, const double *tf, con
 // precision, num_cu): a stencil pass of `tile` with about `target`
 // workgroups, and the one-sweep kernel with `rows` box rows per wavefront.
 GridArgs make_grid(const pot3d_ctx *c, int tile, int target, int ci_fixed);
-GridArgs make_sweep_grid(const pot3d_ctx *c, int rows, int target);
+// widen: sweep_tk's tile width (false: 48 cells).
+GridArgs make_sweep_grid(const pot3d_ctx *c, int rows, int target, bool widen);
 // x update mode of sweep `it` of a captured sequence (SweepVecs::xmode), and
 // the HBM bytes per unknown per iteration of the one-sweep form that go with it.
 int sweep_xmode(int it);

@@ -132,7 +132,8 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     shape.num_cu = ds.num_cu;
 
     GridArgs go = make_grid(&shape, kTileWave2, 2048, 0);
-    GridArgs gs = make_sweep_grid(&shape, 4, ds.sweep_per_cu * ds.num_cu);
+    // 48-cell tiles: the partial sums are part of the scratch that limits a grid's size
+    GridArgs gs = make_sweep_grid(&shape, 4, ds.sweep_per_cu * ds.num_cu, false);
     const int maxblk = std::max(1, std::max(go.nblocks, gs.nblocks));
     const size_t vec = (size_t)shape.npad * sizeof(double);
     size_t off = 0;

@@ -47,3 +47,19 @@ def test_limiting_residual_matches_the_stored_one(case, monkeypatch):
             rr[form] = gpu_solve(s, br, 1e-15, 3000)[3]
     print(f"[limiting residual] {label(case)} {rr}", flush=True)
     assert np.isfinite(rr[P.ITER_ONE_SWEEP]) and rr[P.ITER_ONE_SWEEP] <= 2.0 * rr[P.ITER_TWO_PASS]
+
+
+@pytest.mark.parametrize("np_", [50, 56, 105, 113])
+def test_tile_widths(np_, monkeypatch):
+    """Rows of one 56-cell tile (short of it, and exactly), of one and a part,
+    and rows that stay on 48-cell tiles: the oracle's iterates to the same bar."""
+    monkeypatch.setenv("POT3D_ONCHIP", "0")
+    rf, tf, pf = make_faces(20, 29, np_, "stretched", "ratio3", "jittered")
+    br = magnetograms.br_bipoles(tf, pf, 20, seed=8)
+    coef = oracle.assemble(rf, tf, pf)
+    b = oracle.rhs(rf, tf, pf, br)
+    with P.Solver(rf, tf, pf, iteration=P.ITER_ONE_SWEEP) as s:
+        for K in (1, 2, 5, 8):
+            phi, st, it, _ = gpu_solve(s, br, 0.0, K)
+            assert st == P.ENOCONV and it == K
+            check_solution(phi, oracle.pcg(coef, b, 0.0, K)[0], tol=1e-11)
