@@ -30,8 +30,8 @@
 //   p_j = z_j + beta_j p_{j-1},  w_j = A p_j,  v_j = D^-1 w_j
 // and, with r = D z, the sums r.z, r.r, p.w, z.w, w.v, from which every
 // workgroup forms alpha_j, the predicted r.z and beta_{j+1} for itself.  So a
-// step needs one // exchange between the workgroups, in which the sums and the boundary cells
-// of v travel together: a workgroup keeps z and p of the one-cell ring around
+// step needs one exchange between the workgroups, in which the sums and the
+// boundary cells of v travel together: a workgroup keeps z and p of the one-cell ring around
 // its box too, and with the ring's v it advances them by the same operations
 // as their owner, bit for bit.
 //
