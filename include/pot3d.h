@@ -187,16 +187,17 @@ int pot3d_solve_device(pot3d_ctx *ctx, const double *d_br, const double *d_phi0,
 
 /*
  * y = A x with the solver's own stencil (the Sec. 2.2 operator, volume-scaled).
- * d_x, d_y: device, N each, phi-fastest, distinct.  Ordered on `stream`
- * (NULL = the context's stream); returns after the kernel has completed.
+ * d_x, d_y: device, N each, phi-fastest, distinct; they may overlap in part
+ * (such arrays, and arrays of another device, are copied first).  Ordered on
+ * `stream` (NULL = the context's stream); returns after the kernel has completed.
  */
 int pot3d_apply_device(pot3d_ctx *ctx, const double *d_x, double *d_y, void *stream);
 
 /*
  * z = M^-1 r with the context's preconditioner (pot3d_set_preconditioner:
  * point Jacobi, the diagonal of A, Sec. 2.3; or the phi-line blocks).
- * d_r, d_z: device, N each, phi-fastest, distinct.  FP64 contexts only
- * (POT3D_EINVAL otherwise).  Ordered on `stream` (NULL = the context's);
+ * d_r, d_z: device, N each, phi-fastest, distinct, overlapping as for
+ * pot3d_apply_device.  FP64 contexts only (POT3D_EINVAL otherwise).  Ordered on `stream` (NULL = the context's);
  * returns after the kernel has completed.
  */
 int pot3d_precondition_device(pot3d_ctx *ctx, const double *d_r, double *d_z, void *stream);

@@ -26,6 +26,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -642,6 +643,48 @@ hipError_t copy_rows(void *dst, size_t dpitch, const void *src, size_t spitch, s
                      hipMemcpyKind kind, hipStream_t s)
 {
     return hipMemcpy2DAsync(dst, dpitch, src, spitch, width, rows, kind, s);
+}
+
+// Whether a kernel on the context's device may read n doubles at `in` while it
+// writes n at `out`: both in that device's memory, and apart.
+bool usable_in_place(int device, const double *in, const double *out, long long n)
+{
+    for (const double *p : {in, out}) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (a.type != hipMemoryTypeDevice || a.device != device) return false;
+    }
+    const std::uintptr_t i = reinterpret_cast<std::uintptr_t>(in), o = reinterpret_cast<std::uintptr_t>(out);
+    const std::uintptr_t bytes = (std::uintptr_t)n * sizeof(double);
+    return i + bytes <= o || o + bytes <= i;
+}
+
+// A pass from the caller's packed rows to the caller's packed rows, on s until
+// it has completed: launch(grid, in, out).  Arrays that a kernel can't use in
+// place go through padded rows of the context (p and r, free between solves).
+template <typename F>
+int on_rows(pot3d_ctx *c, const double *in, double *out, hipStream_t s, F launch)
+{
+    if (usable_in_place(c->device, in, out, c->n)) {
+        HIP_TRY(c, launch(c->grid_a, in, out));
+    } else {
+        const size_t rowb = (size_t)c->np * sizeof(double), pitchb = (size_t)c->pitch * sizeof(double);
+        const size_t nrows = (size_t)c->nr * c->nt;
+        GridArgs g = c->grid_a;
+        g.pitch = c->pitch;
+        g.plane = (long long)c->nt * c->pitch;
+        g.npad = c->npad;
+        HIP_TRY(c, copy_rows(c->p[1], pitchb, in, rowb, rowb, nrows, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(c, launch(g, c->p[1], c->r));
+        HIP_TRY(c, copy_rows(out, rowb, c->r, pitchb, rowb, nrows, hipMemcpyDeviceToDevice, s));
+    }
+    HIP_TRY(c, hipStreamSynchronize(s));
+    if (const unsigned line = take_oob_line(s))
+        return fail(c, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
+    return POT3D_OK;
 }
 
 int check_solve_args(pot3d_ctx *c, const void *br, const void *phi, double tol, int maxit)
@@ -1356,15 +1399,13 @@ int pot3d_apply_device(pot3d_ctx *ctx, const double *d_x, double *d_y, void *str
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
-    StencilVecs<double> a = base_vecs(ctx);
-    a.in = d_x;
-    a.y = d_y;
-    a.ignore_done = 1;
-    HIP_TRY(ctx, launch_stencil<double>(kApply, ctx->tile_a, ctx->grid_a, a, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (const unsigned line = take_oob_line(s))
-        return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
-    return POT3D_OK;
+    return on_rows(ctx, d_x, d_y, s, [&](const GridArgs &g, const double *x, double *y) {
+        StencilVecs<double> a = base_vecs(ctx);
+        a.in = x;
+        a.y = y;
+        a.ignore_done = 1;
+        return launch_stencil<double>(kApply, ctx->tile_a, g, a, s);
+    });
 }
 
 int pot3d_precondition_device(pot3d_ctx *ctx, const double *d_r, double *d_z, void *stream)
@@ -1376,14 +1417,10 @@ int pot3d_precondition_device(pot3d_ctx *ctx, const double *d_r, double *d_z, vo
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
-    if (ctx->precond == POT3D_PC_PHI_LINE)
-        HIP_TRY(ctx, launch_line<double>(ctx->grid_a, d_r, d_z, ctx->partial, ctx->line_blocks, s));
-    else
-        HIP_TRY(ctx, launch_jacobi(ctx->grid_a, d_r, d_z, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (const unsigned line = take_oob_line(s))
-        return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
-    return POT3D_OK;
+    return on_rows(ctx, d_r, d_z, s, [&](const GridArgs &g, const double *r, double *z) {
+        return ctx->precond == POT3D_PC_PHI_LINE ? launch_line<double>(g, r, z, ctx->partial, ctx->line_blocks, s)
+                                                 : launch_jacobi(g, r, z, s);
+    });
 }
 
 int pot3d_rhs_device(pot3d_ctx *ctx, const double *d_br, double *d_b, void *stream)
