@@ -755,7 +755,7 @@ int run_fp64(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream_t 
 {
     const bool line = c->precond == POT3D_PC_PHI_LINE;
     const bool sweep = !line && one_sweep(c);
-    const bool chip = sweep && c->oc.m > 0;
+    const bool chip = sweep && c->oc.m > 0 && onchip_open(c->device);
     int rc = start_fp64(c, s, tol, maxit, sweep && !chip);
     if (rc != POT3D_OK) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_loop0, s));
@@ -878,6 +878,9 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
     int launches = 0, total = 0, outer = 0;
     DevScalars out{}, inner{};
     double scale_prev = 0.0;
+    const bool line = c->precond == POT3D_PC_PHI_LINE;
+    const bool sweep = !line && one_sweep(c);
+    const bool chip = sweep && c->oc.m > 0 && onchip_open(c->device);   // of all segments: one continues another
     for (;;) {
         int rc = refined_outer_check(c, s, &out);
         if (rc != POT3D_OK) return rc;
@@ -886,9 +889,6 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
             out.status = POT3D_ENOCONV;
             break;
         }
-        const bool line = c->precond == POT3D_PC_PHI_LINE;
-        const bool sweep = !line && one_sweep(c);
-        const bool chip = sweep && c->oc.m > 0;
         rc = refined_start_inner(c, s, tol, maxit - total, out, outer > 0 ? &inner : nullptr, scale_prev,
                                  line ? kInnerLine : chip ? kInnerOnchip : (sweep ? kInnerSweeps : kInnerTwoPass));
         if (rc != POT3D_OK) return rc;

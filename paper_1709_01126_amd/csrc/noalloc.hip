@@ -161,7 +161,7 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
 
     // the on-chip solve's tables, words and faces, where there is room for them
     shape.device = dev;
-    shape.oc = plan_onchip(&shape);
+    if (onchip_open(dev)) shape.oc = plan_onchip(&shape);
     size_t o_layers = 0, o_polar = 0, o_words = 0, o_faces = 0;
     if (shape.oc.m > 0) {
         o_layers = take(((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer));

@@ -55,12 +55,15 @@
 // All workgroups of a launch must be on the chip at once.  There are at most
 // as many as compute units and each fits one, and the host runs one such
 // launch at a time per device; should they still not come together (another
-// process's work holds compute units), every wait ends after a time limit, the
-// launch reports that it gave up and leaves the caller's vectors alone, and
-// the host solves with sweeps instead.
+// process's work holds compute units), a wait ends after a time limit and sets a
+// flag that the others read while they poll, so that one limit ends them all.
+// The launch then reports that it gave up, and the host starts the solve again
+// from its inputs, in sweeps (x and the exchange's buffers hold partial work).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <mutex>
@@ -76,6 +79,7 @@ namespace {
 constexpr int kOcWaves = 8;                   // polar rows of a box
 constexpr int kOcThreads = kOcWaves * kWave;
 constexpr int kOcSums = 5;
+static_assert(kOnchipStop == kWave, "a lane looks at its own word");
 
 // Relaxed agent-scope accesses of the exchange.
 template <typename P, typename T>
@@ -417,7 +421,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
             for (int u = 0; u < kOcWaves; ++u) part += lds.acc[w][u * kWave + lane];
             part = wave_sum(part);
             // records of 16 bytes, two words each: lane pairs store and read them whole
-            unsigned long long *words = a.words + ((size_t)(seq & 1) * kOcSums + w) * 2 * kOnchipMaxWg;
+            unsigned long long *words = a.words + ((seq & 1) * kOcSums + w) * kOnchipSums + kOnchipStop;
             const unsigned long long tag = (unsigned long long)seq << 32;
             if (lane < 2) put_shared(words + 2 * b + lane, tag | (unsigned)(lane ? __double2hiint(part) : __double2loint(part)));
             bool late = false;
@@ -435,10 +439,11 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
 #pragma unroll
                     for (int u = 0; u < NW; ++u) ok = ok && (unsigned)(got[u] >> 32) == seq;
                     if (__all(ok)) break;
-                    if (((n & 15) == 0 || wait_ticks == 0) && wall_clock64() - t0 >= wait_ticks) {   // bounded: see the top
-                        late = true;
-                        break;
+                    if ((n & 15) == 0 || wait_ticks == 0) {   // bounded: see the top
+                        const bool stopped = __any(get_shared(words - kOnchipStop + lane) != 0);
+                        late = stopped | (wall_clock64() - t0 >= wait_ticks);
                     }
+                    if (late) break;
                 }
                 double s = 0.0;
 #pragma unroll
@@ -457,6 +462,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         __syncthreads();
         if (lds.gave_up) {   // the same for the whole workgroup
             if (tid == 0) put_shared(&a.sc->gave_up, 1);
+            if (tid < 2 * kOcSums) put_shared(a.words + tid * kOnchipSums, 1ull);
             return;
         }
         fetch_ring();   // in flight under the scalars
@@ -613,7 +619,11 @@ OnchipPlan plan_onchip(const pot3d_ctx *c)
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || khz <= 0) khz = 100000;
     // an exchange takes microseconds; two seconds without one means that the workgroups are not all running
-    o.wait_ticks = (long long)(khz * 1e-3 * std::max(0, env_int("POT3D_ONCHIP_WAIT_US", 2000000)));
+    const int wait_us = std::max(0, env_int("POT3D_ONCHIP_WAIT_US", 2000000));
+    o.wait_ticks = (long long)(khz * 1e-3 * wait_us);
+    // 64 waits: where launches never come together, trying costs less than 2 % of the time
+    const int retry_ms = env_int("POT3D_ONCHIP_RETRY_MS", -1);
+    o.retry_s = retry_ms >= 0 ? 1e-3 * retry_ms : 64e-6 * wait_us;
     return o;
 }
 
@@ -642,6 +652,27 @@ std::mutex &onchip_lock(int device)
 {
     static std::mutex locks[64];
     return locks[device & 63];
+}
+
+// By device: when resident launches may be tried again (steady clock, seconds).
+static std::atomic<double> &onchip_closed_until(int device)
+{
+    static std::atomic<double> until[64];
+    return until[device & 63];
+}
+
+static double steady_seconds()
+{
+    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+
+bool onchip_open(int device) { return steady_seconds() >= onchip_closed_until(device).load(); }
+
+void onchip_gave_up(int device, const OnchipPlan &plan)
+{
+    std::atomic<double> &until = onchip_closed_until(device);
+    const double t = steady_seconds() + plan.retry_s;
+    for (double was = until.load(); was < t && !until.compare_exchange_weak(was, t);) {}
 }
 
 template <typename V>
@@ -676,7 +707,10 @@ int run_onchip(pot3d_ctx *c, hipStream_t s, int *launches, DevScalars *final_out
             HIP_TRY(c, hipStreamSynchronize(s));
         }
         ++*launches;
-        if (c->h_sc[0].gave_up) return kOnchipGaveUp;
+        if (c->h_sc[0].gave_up) {
+            onchip_gave_up(c->device, c->oc);
+            return kOnchipGaveUp;
+        }
         if (c->h_sc[0].done) break;
     }
     *final_out = c->h_sc[0];

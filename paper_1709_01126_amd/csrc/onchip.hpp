@@ -31,7 +31,8 @@ struct OnchipPlan {
     int ti = 0, tj = 0, tk = 0, nti = 0, ntj = 0, ntk = 0;
     unsigned seq = 0;                 // number of the last exchange step
     long long wait_ticks = 0;         // longest wait of an exchange (device wall clock)
-    unsigned long long *words = nullptr;   // device: posted sums, [2][5][kOnchipMaxWg][2]
+    double retry_s = 0.0;             // how long the device stays with sweeps after a give-up
+    unsigned long long *words = nullptr;   // device: posted sums, [2][5][kOnchipSums]
     void *faces = nullptr;                 // device: the workgroups' boundary cells (FP64, or FP32 in refined contexts)
     size_t face_bytes = 0;
     OnchipLayer *layers = nullptr;         // device, nr + kOnchipMaxLayers (beyond nr: no couplings, diagonal 1)
@@ -39,7 +40,11 @@ struct OnchipPlan {
 };
 // Boundary cells of a box of m layers, with some cells between the boxes' sets.
 constexpr int onchip_faces(int m) { return 2 * (8 * 64 + m * 64 + m * 8) + 16; }
-constexpr size_t kOnchipWords = 2 * 5 * 2 * (size_t)kOnchipMaxWg;
+// Posted sums of one step and component: kOnchipStop words of which any is set
+// once an exchange has waited too long, then two words per workgroup.
+constexpr int kOnchipStop = 64;
+constexpr int kOnchipSums = kOnchipStop + 2 * kOnchipMaxWg;
+constexpr size_t kOnchipWords = 2 * 5 * (size_t)kOnchipSums;
 
 template <typename V>
 struct OnchipArgs {
@@ -75,6 +80,12 @@ void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper
 // Resident launches of one device run one at a time: held from before a launch
 // until it has completed.
 std::mutex &onchip_lock(int device);
+// Whether a device takes resident launches: not for plan.retry_s after one gave
+// up, since what kept it from coming together (another process's kernels, a
+// stream that may not use every compute unit) is likely still there, and every
+// try costs the whole wait.
+bool onchip_open(int device);
+void onchip_gave_up(int device, const OnchipPlan &plan);
 // One launch on s with the context's vectors (FP64, or the FP32 inner ones);
 // the caller holds the lock and copies the scalars back.
 int queue_onchip(pot3d_ctx *c, int chunk, bool fresh, hipStream_t s);

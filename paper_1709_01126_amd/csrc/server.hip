@@ -137,6 +137,7 @@ struct pot3d_server {
     DevScalars *h_status = nullptr;   // pinned, [3][slot]: statuses after the two latest replays, and of the on-chip slots
     Replay replay[2];
     int last = -1;                    // replay buffer of the most recent launch
+    hipEvent_t chip_done[2] = {nullptr, nullptr};   // the two latest launches of on-chip slots
     std::vector<BatchGraph> graphs;   // captured batched graphs by launch widths
     unsigned long long graph_clock = 0;
     int need_p = 0, need_r = 0;   // workgroups the active slots own in each pass (need_p: the sweep)
@@ -478,7 +479,7 @@ int admit(pot3d_server *sv, Slot &sl, Request *r, pot3d_ctx *c)
     sl.ctx = c;
     sl.req = r;
     sl.active = true;
-    sl.chip = sv->sweep && c->oc.m > 0;
+    sl.chip = sv->sweep && c->oc.m > 0 && onchip_open(sv->device);
     sl.phase = ++sv->next_phase;
     r->t_admit = sv->now();
     SV_TRY(sv, hipEventRecord(c->ev_t0, s));
@@ -548,6 +549,8 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
     hipError_t e = hipStreamCreateWithFlags(&p->stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking);
     for (int b = 0; b < 2 && e == hipSuccess; ++b) {
+        e = hipEventCreateWithFlags(&p->chip_done[b], hipEventDisableTiming);
+        if (e != hipSuccess) break;
         p->replay[b].req.assign(max_slots, nullptr);
         p->replay[b].phase.assign(max_slots, 0);
         e = hipEventCreateWithFlags(&p->replay[b].done, hipEventDisableTiming);
@@ -683,11 +686,15 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         }
     }
     if (chips > 0) {
-        //    small grids advance on chip, one after the other
+        //    small grids advance on chip, one after the other.  One launch runs
+        //    while the one before is looked at: if that has given up, the slots
+        //    behind it don't wait for the same reason in turn.
         DevScalars *h = sv->h_status + 2 * sv->max_slots;
+        bool gave_up = false;
+        std::vector<int> ran;
         {
             std::lock_guard<std::mutex> one(onchip_lock(sv->device));
-            for (int q = 0; q < sv->max_slots; ++q) {
+            for (int q = 0; q < sv->max_slots && !gave_up; ++q) {
                 Slot &sl = sv->slots[q];
                 if (!sl.active || !sl.chip) continue;
                 SV_CALL(sv, sl.ctx, queue_onchip(sl.ctx, kChipSteps, sl.fresh, s));
@@ -695,14 +702,27 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
                 sl.launches += 1;
                 SV_TRY(sv, hipMemcpyAsync(&h[q], sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32,
                                           sizeof(DevScalars), hipMemcpyDeviceToHost, s));
+                const size_t n = ran.size();
+                SV_TRY(sv, hipEventRecord(sv->chip_done[n & 1], s));
+                if (n > 0) {
+                    SV_TRY(sv, hipEventSynchronize(sv->chip_done[(n - 1) & 1]));
+                    gave_up = h[ran.back()].gave_up != 0;
+                }
+                ran.push_back(q);
             }
             SV_TRY(sv, hipStreamSynchronize(s));
         }
         ++sv->replays;
+        for (int q : ran) gave_up = gave_up || h[q].gave_up != 0;
+        if (gave_up) onchip_gave_up(sv->device, sv->slots[ran[0]].ctx->oc);
         for (int q = 0; q < sv->max_slots; ++q) {
             Slot &sl = sv->slots[q];
             if (!sl.active || !sl.chip) continue;
-            if (h[q].gave_up) {   // start again, in the batched sweeps
+            const bool launched_now = std::find(ran.begin(), ran.end(), q) != ran.end();
+            if (launched_now && !h[q].gave_up && h[q].done) {
+                const int rc = ended(sl, h[q]);
+                if (rc != POT3D_OK) return rc;
+            } else if (gave_up) {   // start again, in the batched sweeps
                 pot3d_ctx *c = sl.ctx;
                 c->oc.m = 0;
                 const double t_admit = sl.req->t_admit;
@@ -710,9 +730,6 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
                 if (rc != POT3D_OK) return rc;
                 if (sl.req) sl.req->t_admit = t_admit;
                 changed = true;
-            } else if (h[q].done) {
-                const int rc = ended(sl, h[q]);
-                if (rc != POT3D_OK) return rc;
             }
         }
     }
@@ -848,6 +865,8 @@ void pot3d_server_destroy(pot3d_server *sv)
                     sv->d_r32[0], sv->d_r32[1], sv->d_s64, sv->d_s32, sv->d_finp, sv->d_finr};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
+    for (hipEvent_t ev : sv->chip_done)
+        if (ev) (void)hipEventDestroy(ev);
     if (sv->h_status) (void)hipHostFree(sv->h_status);
     for (Replay &r : sv->replay)
         if (r.done) (void)hipEventDestroy(r.done);
