@@ -624,7 +624,7 @@ void free_ctx(pot3d_ctx *c)
     if (c->stream) (void)hipStreamDestroy(c->stream);
     void *bufs[] = {c->rows, c->dphi, c->ih, c->bfac, c->x, c->r, c->p[0], c->p[1],
                     c->bplane, c->br, c->partial, c->poles, c->vr, c->vt, c->bcs, c->ftab, c->sc,
-                    c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32, c->oc.words, c->oc.layers, c->oc.polar, c->oc.faces};
+                    c->r32, c->p32[0], c->p32[1], c->e32, c->sc32, c->z, c->z32, c->oc.words};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (c->h_sc) (void)hipHostFree(c->h_sc);
@@ -1169,26 +1169,13 @@ int time_sweeps(pot3d_ctx *ctx, V *r, V *p0, V *p1, V *x, DevScalars *sc, int re
     return POT3D_OK;
 }
 
-int create_context(const double *r_faces, int nr, const double *t_faces, int nt, const double *p_faces, int np,
-                   int upper_bc, int precision, int device, bool serving, pot3d_ctx **out)
+void shape_context(pot3d_ctx *c, int nr, int nt, int np, int precision, int device)
 {
-    int v = validate_grid(r_faces, nr, t_faces, nt, p_faces, np, upper_bc, precision, out);
-    if (v != POT3D_OK) return v;
-    *out = nullptr;
-    int ndev = 0;
-    if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return fail(nullptr, POT3D_EDEVICE, "no HIP device");
-    if (device < 0 || device >= ndev) return fail(nullptr, POT3D_EINVAL, "device index out of range");
-    DeviceGuard guard(device);
-    if (!guard.ok) return fail(nullptr, POT3D_EDEVICE, "hipSetDevice failed");
-
-    pot3d_ctx *c = new pot3d_ctx();
     c->device = device;
-    c->serving = serving;
     c->nr = nr;
     c->nt = nt;
     c->np = np;
     c->precision = precision;
-    c->upper_bc = upper_bc;
     // rows padded to an even length at least, so two-cell (16-byte) accesses stay in the row
     int align = std::max(2, env_int("POT3D_PITCH_ALIGN", 8));
     align += align & 1;
@@ -1207,14 +1194,33 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     else
         c->iteration = (precision == POT3D_FP32_REFINED && streams_from_hbm(c)) ? POT3D_ITER_TWO_PASS
                                                                                 : POT3D_ITER_ONE_SWEEP;
+    choose_launch(c);
+    c->oc = plan_onchip(c);
+}
+
+int create_context(const double *r_faces, int nr, const double *t_faces, int nt, const double *p_faces, int np,
+                   int upper_bc, int precision, int device, bool serving, pot3d_ctx **out)
+{
+    int v = validate_grid(r_faces, nr, t_faces, nt, p_faces, np, upper_bc, precision, out);
+    if (v != POT3D_OK) return v;
+    *out = nullptr;
+    int ndev = 0;
+    if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) return fail(nullptr, POT3D_EDEVICE, "no HIP device");
+    if (device < 0 || device >= ndev) return fail(nullptr, POT3D_EINVAL, "device index out of range");
+    DeviceGuard guard(device);
+    if (!guard.ok) return fail(nullptr, POT3D_EDEVICE, "hipSetDevice failed");
+
+    pot3d_ctx *c = new pot3d_ctx();
+    c->serving = serving;
+    c->upper_bc = upper_bc;
+    hipDeviceProp_t prop{};
+    if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
+        c->num_cu = prop.multiProcessorCount;
+    shape_context(c, nr, nt, np, precision, device);
     c->rf.assign(r_faces, r_faces + nr + 1);
     c->tf.assign(t_faces, t_faces + nt + 1);
     c->pf.assign(p_faces, p_faces + np + 1);
     build_tables(c);
-    hipDeviceProp_t prop{};
-    if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
-        c->num_cu = prop.multiProcessorCount;
-    choose_launch(c);
 
     auto bail = [&](hipError_t e, const char *what) {
         std::string m = std::string(what) + ": " + hipGetErrorString(e);
@@ -1265,22 +1271,21 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
     CREATE_TRY(launch_fill<double>(c->bplane, (long long)nt * c->pitch, 0.0, c->stream));
     CREATE_TRY(launch_fill<double>(c->poles, 2LL * nr, 0.0, c->stream));
     CREATE_TRY(hipMemsetAsync(c->sc, 0, sizeof(DevScalars), c->stream));
+    std::vector<OnchipLayer> layers;
+    std::vector<OnchipRow> polar;
+    if (c->oc.m > 0) {
+        void *block = nullptr;
+        CREATE_TRY(hipMalloc(&block, c->oc.bytes));
+        onchip_place(c->oc, nr, nt, block);
+        layers.resize((size_t)nr + kOnchipMaxLayers);
+        polar.resize((size_t)nt);
+        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, layers.data(), polar.data());
+        CREATE_TRY(launch_fill<double>(reinterpret_cast<double *>(c->oc.words), (long long)kOnchipWords, 0.0, c->stream));
+        CREATE_TRY(hipMemcpyAsync(c->oc.layers, layers.data(), layers.size() * sizeof(OnchipLayer), hipMemcpyHostToDevice, c->stream));
+        CREATE_TRY(hipMemcpyAsync(c->oc.polar, polar.data(), polar.size() * sizeof(OnchipRow), hipMemcpyHostToDevice, c->stream));
+    }
     CREATE_TRY(hipStreamSynchronize(c->stream));
     set_tables(c);
-    c->oc = plan_onchip(c);
-    if (c->oc.m > 0) {
-        CREATE_TRY(dalloc(&c->oc.words, kOnchipWords));
-        CREATE_TRY(launch_fill<double>(reinterpret_cast<double *>(c->oc.words), (long long)kOnchipWords, 0.0, c->stream));
-        std::vector<OnchipLayer> layers((size_t)nr + kOnchipMaxLayers);
-        std::vector<OnchipRow> polar((size_t)nt);
-        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, layers.data(), polar.data());
-        CREATE_TRY(dalloc(&c->oc.layers, layers.size()));
-        CREATE_TRY(dalloc(&c->oc.polar, polar.size()));
-        CREATE_TRY(hipMemcpy(c->oc.layers, layers.data(), layers.size() * sizeof(OnchipLayer), hipMemcpyHostToDevice));
-        CREATE_TRY(hipMemcpy(c->oc.polar, polar.data(), polar.size() * sizeof(OnchipRow), hipMemcpyHostToDevice));
-        CREATE_TRY(hipMalloc(&c->oc.faces, c->oc.face_bytes));
-        CREATE_TRY(hipStreamSynchronize(c->stream));
-    }
     if (precision == POT3D_FP32_REFINED) {
         CREATE_TRY(dalloc(&c->r32, (size_t)c->npad));
         CREATE_TRY(dalloc(&c->p32[0], (size_t)c->npad));
@@ -1313,8 +1318,8 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
 
 size_t context_bytes(const pot3d_ctx *c)
 {
-    size_t b = (size_t)c->npad * sizeof(double) * 4 + c->oc.face_bytes + (size_t)c->nt * c->pitch * sizeof(double) +
-               (size_t)c->nt * c->np * sizeof(double) + c->rows_h.size() * sizeof(RowCoef) +
+    size_t b = (size_t)c->npad * sizeof(double) * 4 + c->oc.bytes + (size_t)c->nt * c->pitch * sizeof(double) +
+               (size_t)c->nt * c->np * sizeof(double) + (size_t)c->nr * c->nt * sizeof(RowCoef) +
                (size_t)kMaxPartials * c->max_blocks * sizeof(double) + (size_t)2 * c->nr * sizeof(double);
     if (c->precision == POT3D_FP32_REFINED) b += (size_t)c->npad * sizeof(float) * 4;
     return b;

@@ -153,12 +153,15 @@ double sweep_bytes(bool fp32);
 // that go with it (the phi-line iteration adds 16 N, 8 N in FP32).
 int update_r_mode(int it, int m);
 double two_pass_bytes(bool fp32, int m);
+// Sizes, launch shapes and the on-chip plan of a grid on `device` (num_cu set):
+// all that context_bytes needs.  Allocates nothing on the device.
+void shape_context(pot3d_ctx *c, int nr, int nt, int np, int precision, int device);
 // Allocate a context on `device` (tables, vectors, graphs).  serving = true:
 // no graph capture (the server's batched graph iterates it).
 int create_context(const double *rf, int nr, const double *tf, int nt, const double *pf, int np, int upper_bc,
                    int precision, int device, bool serving, pot3d_ctx **out);
 void free_ctx(pot3d_ctx *c);
-// Device bytes held by a context.
+// Device bytes held by a context (of that shape).
 size_t context_bytes(const pot3d_ctx *c);
 StencilVecs<double> base_vecs(pot3d_ctx *c);
 // b from Br (device) and the starting x (phi0 or zero).

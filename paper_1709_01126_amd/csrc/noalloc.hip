@@ -162,12 +162,9 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
     // the on-chip solve's tables, words and faces, where there is room for them
     shape.device = dev;
     if (onchip_open(dev)) shape.oc = plan_onchip(&shape);
-    size_t o_layers = 0, o_polar = 0, o_words = 0, o_faces = 0;
+    size_t o_chip = 0;
     if (shape.oc.m > 0) {
-        o_layers = take(((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer));
-        o_polar = take((size_t)nt * sizeof(OnchipRow));
-        o_words = take(kOnchipWords * sizeof(unsigned long long));
-        o_faces = take(shape.oc.face_bytes);
+        o_chip = take(shape.oc.bytes);
         if (off > kScratchBytes) shape.oc.m = 0;
     }
 
@@ -243,10 +240,7 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
         shape.p[1] = pb[1];
         shape.sc = sc;
         shape.h_sc = &h_sc;
-        shape.oc.layers = reinterpret_cast<OnchipLayer *>(base + o_layers);
-        shape.oc.polar = reinterpret_cast<OnchipRow *>(base + o_polar);
-        shape.oc.words = reinterpret_cast<unsigned long long *>(base + o_words);
-        shape.oc.faces = base + o_faces;
+        onchip_place(shape.oc, nr, nt, base + o_chip);
         onchip_tables(nr, nt, r_faces, t_faces, upper_bc, h_layers, h_polar);
         NA_TRY(hipMemcpyAsync(shape.oc.layers, h_layers, ((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer), hipMemcpyHostToDevice, s));
         NA_TRY(hipMemcpyAsync(shape.oc.polar, h_polar, (size_t)nt * sizeof(OnchipRow), hipMemcpyHostToDevice, s));

@@ -616,6 +616,7 @@ OnchipPlan plan_onchip(const pot3d_ctx *c)
     o.ntk = (c->np + o.tk - 1) / o.tk;
     o.face_bytes = 2 * (size_t)(o.nti * o.ntj * o.ntk) * onchip_faces(o.m) *
                    (c->precision == POT3D_FP32_REFINED ? sizeof(float) : sizeof(double));
+    onchip_place(o, c->nr, c->nt, nullptr);   // bytes
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device) != hipSuccess || khz <= 0) khz = 100000;
     // an exchange takes microseconds; two seconds without one means that the workgroups are not all running
@@ -625,6 +626,21 @@ OnchipPlan plan_onchip(const pot3d_ctx *c)
     const int retry_ms = env_int("POT3D_ONCHIP_RETRY_MS", -1);
     o.retry_s = retry_ms >= 0 ? 1e-3 * retry_ms : 64e-6 * wait_us;
     return o;
+}
+
+void onchip_place(OnchipPlan &o, int nr, int nt, void *base)
+{
+    auto padded = [](size_t n) { return (n + 255) & ~size_t(255); };
+    const size_t layers = padded(kOnchipWords * sizeof(*o.words));
+    const size_t polar = layers + padded(((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer));
+    const size_t faces = polar + padded((size_t)nt * sizeof(OnchipRow));
+    o.bytes = faces + o.face_bytes;
+    if (!base) return;
+    char *const b = static_cast<char *>(base);
+    o.words = reinterpret_cast<unsigned long long *>(b);
+    o.layers = reinterpret_cast<OnchipLayer *>(b + layers);
+    o.polar = reinterpret_cast<OnchipRow *>(b + polar);
+    o.faces = b + faces;
 }
 
 void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper_bc, OnchipLayer *layers,

@@ -35,6 +35,7 @@ struct OnchipPlan {
     unsigned long long *words = nullptr;   // device: posted sums, [2][5][kOnchipSums]
     void *faces = nullptr;                 // device: the workgroups' boundary cells (FP64, or FP32 in refined contexts)
     size_t face_bytes = 0;
+    size_t bytes = 0;                      // of the four arrays together (onchip_place)
     OnchipLayer *layers = nullptr;         // device, nr + kOnchipMaxLayers (beyond nr: no couplings, diagonal 1)
     OnchipRow *polar = nullptr;            // device, nt
 };
@@ -77,6 +78,8 @@ OnchipPlan plan_onchip(const pot3d_ctx *c);
 // Host tables of the operator's factors (nr + kOnchipMaxLayers layers, nt polar rows).
 void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper_bc, OnchipLayer *layers,
                    OnchipRow *polar);
+// The plan's arrays in `bytes` of device memory at base, words first.
+void onchip_place(OnchipPlan &o, int nr, int nt, void *base);
 // Resident launches of one device run one at a time: held from before a launch
 // until it has completed.
 std::mutex &onchip_lock(int device);

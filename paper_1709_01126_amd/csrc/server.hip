@@ -70,6 +70,7 @@ struct Request {
     double relres_true = 0.0;
     double t_submit = 0.0, t_admit = -1.0, t_done = -1.0;
     bool done = false;
+    size_t device_bytes = 0;   // of its context (size_request; 0: not yet known)
     int overtaken = 0;   // later requests admitted while this one waited for streaming budget
 };
 
@@ -109,7 +110,7 @@ int round_up(int v, int a) { return (v + a - 1) / a * a; }
 }  // namespace
 
 struct pot3d_server {
-    int device = 0, precision = POT3D_FP64, max_slots = 0, graph_m = 16;
+    int device = 0, num_cu = 256, precision = POT3D_FP64, max_slots = 0, graph_m = 16;
     int tile_p = kTileMarch8, tile_r = kTileMarch8;   // launch shapes of every slot
     bool sweep = true;       // one-sweep batches (else two passes)
     int sweep_rows = 4;      // box rows per wavefront of every slot's sweep kernel
@@ -377,6 +378,17 @@ void evict_one(pot3d_server *sv)
     free_ctx(c);
 }
 
+// What the request will hold.
+void size_request(const pot3d_server *sv, Request *r)
+{
+    if (r->device_bytes) return;
+    pot3d_ctx shape;   // owns nothing
+    shape.serving = true;
+    shape.num_cu = sv->num_cu;
+    shape_context(&shape, r->nr, r->nt, r->np, sv->precision, sv->device);
+    r->device_bytes = context_bytes(&shape);
+}
+
 // A context for r: a cached one with the same grid, or a new one if the budget
 // allows (evicting idle contexts oldest first).  *ctx = NULL: not now.
 int acquire_context(pot3d_server *sv, Request *r, pot3d_ctx **ctx)
@@ -389,13 +401,8 @@ int acquire_context(pot3d_server *sv, Request *r, pot3d_ctx **ctx)
             return POT3D_OK;
         }
     }
-    // estimate before allocating: 4 FP64 vectors (+4 FP32 in refined mode) of the
-    // padded size, plus tables; one vector more in the one-sweep form, as room
-    // for the tables and sums of the smallest grids
-    const long long pitch = (r->np + 7) / 8 * 8;
-    const size_t per_cell = sv->precision == POT3D_FP32_REFINED ? (sv->sweep ? 52 : 48) : (sv->sweep ? 40 : 32);
-    const size_t need = (size_t)r->nr * r->nt * pitch * per_cell +
-                        (size_t)r->nr * r->nt * 64 + (size_t)r->nt * pitch * 16 + (1u << 20);
+    size_request(sv, r);
+    const size_t need = r->device_bytes;
     while (sv->used + need > sv->budget && !sv->idle.empty()) evict_one(sv);
     if (sv->used + need > sv->budget) return POT3D_OK;   // wait for a slot to retire
     pot3d_ctx *c = nullptr;
@@ -523,6 +530,9 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
     sv->precision = precision;
     sv->max_slots = max_slots;
     sv->t0 = std::chrono::steady_clock::now();
+    hipDeviceProp_t prop{};
+    if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
+        sv->num_cu = prop.multiProcessorCount;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return sfail(nullptr, POT3D_EDEVICE, "hipMemGetInfo failed");
     sv->budget = hbm_budget_bytes > 0.0 ? (size_t)hbm_budget_bytes : (size_t)(0.8 * (double)free_b);
