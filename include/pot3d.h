@@ -353,10 +353,11 @@ const char *pot3d_version(void);
  * host.  Each pot3d_server_step:
  *   1. retires the solves that ended in the previous step;
  *   2. admits queued requests, in order, while a slot is free, their device
- *      memory fits the budget, and the bytes that the active solves stream
- *      per iteration stay within the cache budget (or no solve is active);
- *      a request that does not fit beside the active solves may be passed
- *      by up to 8 later ones that do, then waits at the head;
+ *      memory fits the budget, and the bytes that the active solves of the
+ *      same kind (in the batch, or on chip) stream per iteration stay within
+ *      the cache budget (or no such solve is active); a request that does not
+ *      fit beside them may be passed by up to 8 later ones that do, then its
+ *      kind waits behind it;
  *   3. advances every active solve by a fixed number of PCG iterations
  *      (32 sweeps in the one-sweep form, 16 two-pass iterations otherwise;
  *      the form is POT3D_ITERATION's when the server is created, one sweep
@@ -442,7 +443,8 @@ int pot3d_server_result(pot3d_server *sv, long long id, double *phi, pot3d_reque
 /*
  * Streaming budget of the batch: a request joins the active solves only if
  * the bytes they all stream per iteration (32 per cell in FP64, 16 in refined
- * mode) stay within `bytes`, or if none is active.  Default 256 MiB, the
+ * mode) stay within `bytes`, or if none is active; solves that run on chip
+ * and solves of the batch are counted apart.  Default 256 MiB, the
  * memory-side cache of the device: solves that run from it alone are not
  * slowed by batching, and bandwidth-bound ones run alone, since batching
  * cannot speed them up.  0 removes the limit.
