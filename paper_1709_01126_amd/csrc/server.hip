@@ -8,8 +8,9 @@
 //      retirement;
 //   2. admits queued requests, in arrival order, while a slot is free, their
 //      device footprint fits the HBM budget, and the bytes that all active
-//      solves stream per iteration stay within the cache budget (by default
-//      the 256 MB memory-side cache) -- or the server is idle.  Solves that
+//      solves of the batch stream per iteration stay within the cache budget
+//      (by default the 256 MB memory-side cache) -- or none is active; the
+//      solves on chip (3.) are counted by themselves.  Solves that
 //      run from the cache alone are thus not batched into ones that would
 //      stream from HBM, and bandwidth-bound solves, which batching cannot
 //      speed up, run alone.  A request that does not fit beside the running
@@ -25,12 +26,15 @@
 //      memory maps workgroups to slots), and slots that have converged are
 //      masked by their own done flags.  A slot whose grid the on-chip kernel
 //      fits takes no part in the batch: it advances by a bounded number of
-//      iterations in that kernel, after the replay, one slot after the other.
+//      iterations in that kernel, before the replay, one slot after the other.
 // A step queues its replay before it reads the statuses of the previous one,
 // so in steps where no solve ends or starts the device has the next replay
-// queued while the host decides.  A step that retires or admits a request
-// waits for the stream (Phi out, the refined mode's outer check, the slot
-// tables), so the pipeline drains there.  A slot that finished in replay k
+// queued while the host decides.  With on-chip slots it first waits for the
+// last replay, since resident launches hold a lock of the device that is not
+// to wait for other work; the host then decides while the replay behind them
+// runs.  A step that retires or admits a request waits for the stream (Phi
+// out, the refined mode's outer check, the slot tables), so the pipeline
+// drains there.  A slot that finished in replay k
 // runs through replay k+1 as a no-op, and retirement and admission are
 // ordered after it on the same stream.
 // The graphs read the slot tables at run time, so requests join and leave
@@ -635,16 +639,45 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
     if (!guard.ok) return sfail(sv, POT3D_EDEVICE, "hipSetDevice failed");
     hipStream_t s = sv->stream;
     const int prev = sv->last;
-    // 1. queue the next replay of the active slots (the tables are current),
-    //    with a copy of each slot's scalars after it
-    int launched = -1;
     int batched = 0, chips = 0;
     for (const Slot &sl : sv->slots) (sl.chip ? chips : batched) += sl.active ? 1 : 0;
+    hipGraphExec_t g = nullptr;
     if (batched > 0) {
-        const int b = prev == 0 ? 1 : 0;
-        hipGraphExec_t g = nullptr;
         const int rc = graph_for(sv, sv->need_p, sv->need_r, &g);
         if (rc != POT3D_OK) return rc;
+    }
+    // 1. small grids advance on chip, one after the other.  One launch runs while
+    //    the one before is looked at: if that has given up, the slots behind it
+    //    don't wait for the same reason in turn.
+    DevScalars *const chip_status = sv->h_status + 2 * sv->max_slots;
+    bool gave_up = false;
+    std::vector<int> ran;
+    std::unique_lock<std::mutex> resident(onchip_lock(sv->device), std::defer_lock);
+    if (chips > 0) {
+        SV_TRY(sv, hipStreamSynchronize(s));   // so the lock is not held for the last replay and what came after it
+        resident.lock();
+        for (int q = 0; q < sv->max_slots && !gave_up; ++q) {
+            Slot &sl = sv->slots[q];
+            if (!sl.active || !sl.chip) continue;
+            SV_CALL(sv, sl.ctx, queue_onchip(sl.ctx, kChipSteps, sl.fresh, s));
+            sl.fresh = false;
+            sl.launches += 1;
+            SV_TRY(sv, hipMemcpyAsync(&chip_status[q], sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32,
+                                      sizeof(DevScalars), hipMemcpyDeviceToHost, s));
+            const size_t n = ran.size();
+            SV_TRY(sv, hipEventRecord(sv->chip_done[n & 1], s));
+            if (n > 0) {
+                SV_TRY(sv, hipEventSynchronize(sv->chip_done[(n - 1) & 1]));
+                gave_up = chip_status[ran.back()].gave_up != 0;
+            }
+            ran.push_back(q);
+        }
+    }
+    // 2. queue the next replay of the active slots (the tables are current),
+    //    with a copy of each slot's scalars after it
+    int launched = -1;
+    if (batched > 0) {
+        const int b = prev == 0 ? 1 : 0;
         SV_TRY(sv, hipGraphLaunch(g, s));
         ++sv->replays;
         Replay &rp = sv->replay[b];
@@ -662,7 +695,14 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         rp.pending = true;
         launched = b;
     }
-    // 2. slots whose current solve ended in the previous replay (the one just
+    if (chips > 0) {   // the replay runs on; the resident launches are over
+        SV_TRY(sv, hipEventSynchronize(sv->chip_done[(ran.size() - 1) & 1]));
+        resident.unlock();
+        ++sv->replays;
+        for (int q : ran) gave_up = gave_up || chip_status[q].gave_up != 0;
+        if (gave_up) onchip_gave_up(sv->device, sv->slots[ran[0]].ctx->oc);
+    }
+    // 3. slots whose current solve ended in the previous replay (the one just
     //    queued is a no-op for them; what follows is ordered after it)
     bool changed = false;
     auto ended = [&](Slot &sl, const DevScalars &st) -> int {
@@ -695,42 +735,13 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
             if (rc != POT3D_OK) return rc;
         }
     }
-    if (chips > 0) {
-        //    small grids advance on chip, one after the other.  One launch runs
-        //    while the one before is looked at: if that has given up, the slots
-        //    behind it don't wait for the same reason in turn.
-        DevScalars *h = sv->h_status + 2 * sv->max_slots;
-        bool gave_up = false;
-        std::vector<int> ran;
-        {
-            std::lock_guard<std::mutex> one(onchip_lock(sv->device));
-            for (int q = 0; q < sv->max_slots && !gave_up; ++q) {
-                Slot &sl = sv->slots[q];
-                if (!sl.active || !sl.chip) continue;
-                SV_CALL(sv, sl.ctx, queue_onchip(sl.ctx, kChipSteps, sl.fresh, s));
-                sl.fresh = false;
-                sl.launches += 1;
-                SV_TRY(sv, hipMemcpyAsync(&h[q], sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32,
-                                          sizeof(DevScalars), hipMemcpyDeviceToHost, s));
-                const size_t n = ran.size();
-                SV_TRY(sv, hipEventRecord(sv->chip_done[n & 1], s));
-                if (n > 0) {
-                    SV_TRY(sv, hipEventSynchronize(sv->chip_done[(n - 1) & 1]));
-                    gave_up = h[ran.back()].gave_up != 0;
-                }
-                ran.push_back(q);
-            }
-            SV_TRY(sv, hipStreamSynchronize(s));
-        }
-        ++sv->replays;
-        for (int q : ran) gave_up = gave_up || h[q].gave_up != 0;
-        if (gave_up) onchip_gave_up(sv->device, sv->slots[ran[0]].ctx->oc);
+    if (chips > 0) {   // ... and on chip
         for (int q = 0; q < sv->max_slots; ++q) {
             Slot &sl = sv->slots[q];
             if (!sl.active || !sl.chip) continue;
             const bool launched_now = std::find(ran.begin(), ran.end(), q) != ran.end();
-            if (launched_now && !h[q].gave_up && h[q].done) {
-                const int rc = ended(sl, h[q]);
+            if (launched_now && !chip_status[q].gave_up && chip_status[q].done) {
+                const int rc = ended(sl, chip_status[q]);
                 if (rc != POT3D_OK) return rc;
             } else if (gave_up) {   // start again, in the batched sweeps
                 pot3d_ctx *c = sl.ctx;
@@ -744,7 +755,7 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         }
     }
     sv->last = launched;
-    // 3. admissions
+    // 4. admissions
     // The streaming budget holds for the solves of the batched graph, which share
     // the memory-side cache in every iteration, and by itself for those on chip,
     // which run one after the other and touch memory between their launches:

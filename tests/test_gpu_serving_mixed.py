@@ -3,8 +3,11 @@
 * Neither kind waits for the other's streaming budget: with one batched solve
   filling it, on-chip requests behind a second, waiting one are all done before
   that one is admitted.
-* Every result is bitwise the single solve's.
+* Every result is bitwise the single solve's, with other on-chip solves of the
+  device on another thread meanwhile, whose results are too.
 """
+import threading
+
 import numpy as np
 import pytest
 
@@ -38,3 +41,32 @@ def test_small_requests_run_beside_a_batched_one(precision):
     assert max(t_done[q] for q in (1, 3, 4, 5, 6, 7)) < t_admit[2]
     for (phi_a, st_a, it_a, _), (phi_s, info) in zip(ref, out):
         assert info["status"] == st_a == P.OK and info["iters"] == it_a and np.array_equal(phi_s, phi_a)
+
+
+def test_server_and_single_solves_on_two_threads():
+    reqs = requests([FLAT, SMALL, SMALL, SMALL], tol=1e-9)
+    ref = alone(reqs, P.FP64)
+    _, rf, tf, pf, br, tol, maxit = reqs[1]
+    got, stop = [], threading.Event()
+
+    def singles():
+        with P.Solver(rf, tf, pf) as s:
+            while not stop.is_set():
+                got.append(s.solve(br, tol, maxit))
+
+    th = threading.Thread(target=singles)
+    with P.Server(max_slots=8) as sv:
+        ids = [sv.submit(f0, f1, f2, b, t, m) for _, f0, f1, f2, b, t, m in reqs]
+        th.start()
+        try:
+            for _ in range(100_000):
+                if sv.step()[2] == len(ids) and len(got) >= 2:
+                    break
+        finally:
+            stop.set()
+            th.join()
+        out = [sv.take(rid) for rid in ids]
+    for (phi_a, st_a, it_a, _), (phi_s, info) in zip(ref, out):
+        assert info["status"] == st_a == P.OK and info["iters"] == it_a and np.array_equal(phi_s, phi_a)
+    for phi, st, it, _ in got:
+        assert st == P.OK and it == ref[1][2] and np.array_equal(phi, ref[1][0])
