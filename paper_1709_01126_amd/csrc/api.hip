@@ -682,8 +682,8 @@ int on_rows(pot3d_ctx *c, const double *in, double *out, hipStream_t s, F launch
         HIP_TRY(c, copy_rows(out, rowb, c->r, pitchb, rowb, nrows, hipMemcpyDeviceToDevice, s));
     }
     HIP_TRY(c, hipStreamSynchronize(s));
-    if (const unsigned line = take_oob_line(s))
-        return fail(c, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
+    if (const std::string at = take_oob(s); !at.empty())
+        return fail(c, POT3D_EDEVICE, "checked build: out-of-range index at " + at);
     return POT3D_OK;
 }
 
@@ -978,8 +978,8 @@ int finish_solve(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStrea
     st.n = c->n;
     st.pitch = c->pitch;
     fill_shape(c, st);
-    if (const unsigned line = take_oob_line(s))
-        return fail(c, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
+    if (const std::string at = take_oob(s); !at.empty())
+        return fail(c, POT3D_EDEVICE, "checked build: out-of-range index at " + at);
     c->have_solution = true;
     c->field_ready = true;
     if (iters) *iters = total_iters;
@@ -1511,8 +1511,8 @@ int pot3d_time_kernels(pot3d_ctx *ctx, int reps, double *ms_update_p, double *ms
     ctx->have_solution = false;
     ctx->field_ready = false;
     if (rc == POT3D_OK) {
-        if (const unsigned line = take_oob_line(ctx->stream))
-            return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at kernels.hip line " + std::to_string(line));
+        if (const std::string at = take_oob(ctx->stream); !at.empty())
+            return fail(ctx, POT3D_EDEVICE, "checked build: out-of-range index at " + at);
     }
     return rc;
 }

@@ -2031,21 +2031,23 @@ hipError_t launch_repack(const double *src, double *dst, long long nrows, int np
     return hipGetLastError();
 }
 
-unsigned take_oob_line(hipStream_t s)
+std::string take_oob(hipStream_t s)
 {
+    std::string at;
 #ifdef POT3D_CHECKED
-    unsigned line = 0;
-    if (hipStreamSynchronize(s) != hipSuccess) return ~0u;
-    if (hipMemcpyFromSymbol(&line, HIP_SYMBOL(g_oob_line), sizeof(line)) != hipSuccess) return ~0u;
-    if (line) {
-        const unsigned zero = 0;
-        (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
-    }
-    return line ? line : (onchip_oob_line() | line_oob_line());
+    if (hipStreamSynchronize(s) != hipSuccess) return "an unknown place (the stream failed)";
+    struct Source {
+        const char *file;
+        unsigned (*line)();
+    };
+    for (const Source &src : {Source{"kernels.hip", read_oob_line}, Source{"onchip.hip", onchip_oob_line},
+                              Source{"line.hip", line_oob_line}})
+        if (const unsigned line = src.line())
+            at += (at.empty() ? "" : " and ") + std::string(src.file) + " line " + std::to_string(line);
 #else
     (void)s;
-    return 0;
 #endif
+    return at;
 }
 
 bool checked_build()

@@ -1,6 +1,8 @@
 // kernels.hpp -- launchers of the gfx950 kernels (defined in kernels.hip).
 #pragma once
 
+#include <string>
+
 #include "pot3d.h"
 #include "solver.hpp"
 
@@ -53,9 +55,10 @@ hipError_t launch_sweep_batch(int rows, const BatchSweep<V> *slots, int nslots, 
                               hipStream_t s);
 inline bool valid_sweep_rows(int rows) { return rows == 4 || rows == 6 || rows == 8; }
 
-// Checked builds: the source line of the first out-of-range index seen since
-// the last call (0 if none), after waiting for stream s.  Normal builds: 0.
-unsigned take_oob_line(hipStream_t s);
+// Checked builds: file and line of an out-of-range index in each source that
+// has seen one since the last call (empty if none), after waiting for stream s.
+// Normal builds: empty.
+std::string take_oob(hipStream_t s);
 bool checked_build();
 
 // e0 (optional): an event stamped with the dispatch's start.
@@ -97,7 +100,7 @@ hipError_t launch_line(const GridArgs &g, const V *r, V *z, double *partial, int
 // ntj groups of kWaves polar rows, nblocks workgroups that share them.
 template <typename V>
 hipError_t launch_line_iteration(const GridArgs &g, const SweepVecs<V> &v, hipStream_t s);
-unsigned line_oob_line();   // checked builds, as take_oob_line
+unsigned line_oob_line();   // take_oob's line of line.hip, 0 if none
 // Workgroups of the line pass, or of the line iteration, resident per CU (0 if unknown).
 template <typename V>
 int line_blocks_per_cu(int np, bool iteration);

@@ -657,19 +657,6 @@ int line_blocks_per_cu(int np, bool iteration)
 template int line_blocks_per_cu<double>(int, bool);
 template int line_blocks_per_cu<float>(int, bool);
 
-unsigned line_oob_line()
-{
-#ifdef POT3D_CHECKED
-    unsigned line = 0;
-    if (hipMemcpyFromSymbol(&line, HIP_SYMBOL(g_oob_line), sizeof(line)) != hipSuccess) return ~0u;
-    if (line) {
-        const unsigned zero = 0;
-        (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
-    }
-    return line;
-#else
-    return 0;
-#endif
-}
+unsigned line_oob_line() { return read_oob_line(); }
 
 }  // namespace pot3d

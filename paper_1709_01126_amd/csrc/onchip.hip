@@ -295,19 +295,30 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
     // faces of workgroup g in step s: [2][8][64] below and above, [2][M][64]
     // south and north, [2][8][M] left and right
     constexpr int kFaceJ = 2 * kOcWaves * kWave, kFaceK = kFaceJ + 2 * M * kWave;
-    auto faces = [&](unsigned s, int g) { return to_global(a.faces) + ((s & 1) * nwg + g) * onchip_faces(M); };
+    auto faces = [&](unsigned s, int g) { return to_global(a.faces) + CHK((s & 1) * nwg + g, 2 * nwg) * onchip_faces(M); };
+    // base + c1 + c2 ..: a place among the n from base (summed up otherwise, the
+    // addresses took more registers and M = 16 0.6 us more per step)
+    auto within = [](int n, auto base, auto... c) {
+#ifdef POT3D_CHECKED
+        return base + CHK((c + ...), n);
+#else
+        (void)n;
+        return (base + ... + c);
+#endif
+    };
+    constexpr int kFaces = onchip_faces(M), kWords = 2 * kOnchipMaxWg;
     const int step_i = a.ntk * a.ntj;
     const int g_k = kside ? (kt + 1 < a.ntk ? b + 1 : b + 1 - a.ntk) : (kt > 0 ? b - 1 : b + a.ntk - 1);
     auto fetch_ring = [&]() {
         asm volatile("" : "+v"(lane_off), "+v"(own_p));
-        if (lo_on) v_lo = get_shared(faces(seq, b - step_i) + (kOcWaves + w) * kWave + lane);
-        if (hi_on) v_hi = get_shared(faces(seq, b + step_i) + w * kWave + lane);
+        if (lo_on) v_lo = get_shared(within(kFaces, faces(seq, b - step_i), (kOcWaves + w) * kWave, lane));
+        if (hi_on) v_hi = get_shared(within(kFaces, faces(seq, b + step_i), w * kWave, lane));
 #pragma unroll
         for (int n = 0; n < NJ; ++n) {
             const int far = j_side(n) ? 0 : M;   // the north neighbour's first row, or the south one's last
-            if (j_on(n)) v_j[n] = get_shared(faces(seq, j_side(n) ? b + a.ntk : b - a.ntk) + kFaceJ + (far + j_layer(n)) * kWave + lane);
+            if (j_on(n)) v_j[n] = get_shared(within(kFaces, faces(seq, j_side(n) ? b + a.ntk : b - a.ntk), kFaceJ, (far + j_layer(n)) * kWave, lane));
         }
-        if (k_on) v_k = get_shared(faces(seq, g_k) + kFaceK + ((kside ? 0 : kOcWaves) + kcol) * M + km);
+        if (k_on) v_k = get_shared(within(kFaces, faces(seq, g_k), kFaceK, ((kside ? 0 : kOcWaves) + kcol) * M, km));
     };
 
     for (int step = 0; step < chunk; ++step) {
@@ -385,13 +396,13 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         }
         const GPtr<V> face = faces(seq, b);
         if (own) {
-            put_shared(face + w * kWave + lane, v[0]);
-            if (tin == M) put_shared(face + (kOcWaves + w) * kWave + lane, v[M - 1]);   // else nothing lies above
+            put_shared(within(kFaces, face, w * kWave, lane), v[0]);
+            if (tin == M) put_shared(within(kFaces, face, (kOcWaves + w) * kWave, lane), v[M - 1]);   // else nothing lies above
 #pragma unroll
             for (int side = 0; side < 2; ++side)
                 if (w == (side ? tjn - 1 : 0)) {
 #pragma unroll
-                    for (int m = 0; m < M; ++m) put_shared(face + kFaceJ + (side * M + m) * kWave + lane, v[m]);
+                    for (int m = 0; m < M; ++m) put_shared(within(kFaces, face, kFaceJ, (side * M + m) * kWave, lane), v[m]);
                 }
             // left and right: gathered in LDS, so that they go out as whole lines
 #pragma unroll
@@ -404,7 +415,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         wave_sync();
         if (w < tjn && lane < 2 * M) {
             const int side = lane >= M;
-            put_shared(face + kFaceK + (side * kOcWaves + w) * M + (lane - side * M), lds.edge[w][lane]);
+            put_shared(within(kFaces, face, kFaceK, (side * kOcWaves + w) * M, lane - side * M), lds.edge[w][lane]);
         }
         lds.acc[0][tid] = acc0;
         lds.acc[1][tid] = acc1;
@@ -423,7 +434,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
             // records of 16 bytes, two words each: lane pairs store and read them whole
             unsigned long long *words = a.words + ((seq & 1) * kOcSums + w) * kOnchipSums + kOnchipStop;
             const unsigned long long tag = (unsigned long long)seq << 32;
-            if (lane < 2) put_shared(words + 2 * b + lane, tag | (unsigned)(lane ? __double2hiint(part) : __double2loint(part)));
+            if (lane < 2) put_shared(within(kWords, words, 2 * b, lane), tag | (unsigned)(lane ? __double2hiint(part) : __double2loint(part)));
             bool late = false;
             auto await = [&](auto loads) -> double {   // loads: reads of 64 words that cover the records
                 constexpr int NW = decltype(loads)::value;
@@ -434,7 +445,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
 #pragma unroll
                     for (int u = 0; u < NW; ++u) {
                         got[u] = tag;
-                        if (u * kWave + lane < 2 * nwg) got[u] = get_shared(words + u * kWave + lane);
+                        if (u * kWave + lane < 2 * nwg) got[u] = get_shared(within(kWords, words, u * kWave, lane));
                     }
 #pragma unroll
                     for (int u = 0; u < NW; ++u) ok = ok && (unsigned)(got[u] >> 32) == seq;
@@ -558,20 +569,7 @@ hipError_t launch_onchip(const OnchipArgs<V> &a, int m, int chunk, unsigned seq0
 template hipError_t launch_onchip<double>(const OnchipArgs<double> &, int, int, unsigned, int, long long, hipStream_t);
 template hipError_t launch_onchip<float>(const OnchipArgs<float> &, int, int, unsigned, int, long long, hipStream_t);
 
-unsigned onchip_oob_line()
-{
-#ifdef POT3D_CHECKED
-    unsigned line = 0;
-    if (hipMemcpyFromSymbol(&line, HIP_SYMBOL(g_oob_line), sizeof(line)) != hipSuccess) return ~0u;
-    if (line) {
-        const unsigned zero = 0;
-        (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
-    }
-    return line;
-#else
-    return 0;
-#endif
-}
+unsigned onchip_oob_line() { return read_oob_line(); }
 
 namespace host {
 

@@ -69,7 +69,7 @@ struct OnchipArgs {
 template <typename V>
 hipError_t launch_onchip(const OnchipArgs<V> &a, int m, int chunk, unsigned seq0, int fresh, long long wait_ticks,
                          hipStream_t s);
-unsigned onchip_oob_line();   // checked builds, as take_oob_line
+unsigned onchip_oob_line();   // take_oob's line of onchip.hip, 0 if none
 
 namespace host {
 

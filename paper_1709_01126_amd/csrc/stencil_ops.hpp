@@ -26,6 +26,18 @@ __device__ __forceinline__ long long chk_index(long long i, long long n, unsigne
 #define CHK(i, n) (i)
 #endif
 
+// The line that this source file's kernels have recorded (0: none), cleared.
+static inline unsigned read_oob_line()
+{
+    unsigned line = 0;
+#ifdef POT3D_CHECKED
+    const unsigned zero = 0;
+    if (hipMemcpyFromSymbol(&line, HIP_SYMBOL(g_oob_line), sizeof(line)) != hipSuccess) return ~0u;
+    if (line) (void)hipMemcpyToSymbol(HIP_SYMBOL(g_oob_line), &zero, sizeof(zero));
+#endif
+    return line;
+}
+
 template <typename V> __device__ __forceinline__ V vfma(V a, V b, V c);
 template <> __device__ __forceinline__ double vfma<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <> __device__ __forceinline__ float vfma<float>(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
