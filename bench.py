@@ -35,8 +35,9 @@ HBM_PEAK_GBS = 8000.0
 
 
 def kernel_source_hash() -> str:
+    """Of the sources of the kernels in KERNEL_KEYS and what they include."""
     h = hashlib.sha256()
-    for name in ("kernels.hip", "stencil_ops.hpp", "solver.hpp"):
+    for name in ("kernels.hip", "line.hip", "stencil_ops.hpp", "solver.hpp"):
         with open(os.path.join(ROOT, "paper_1709_01126_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -59,7 +60,6 @@ def load_traffic(workload: str, kernel: str):
 
 
 # algorithmic bytes per unknown of each iteration kernel, and the kernel-name
-# fragments that identify it in a trace
 # fragments that identify it in a trace.  One-sweep form: the even sweeps
 # leave x to the odd ones (24 N: read the last two directions, write the new
 # one), the odd sweeps update x for both (40 N: also read and write x); "sweep" is the sweep that
