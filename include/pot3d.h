@@ -113,7 +113,8 @@ typedef struct pot3d_stats {
                                 in refined mode)                                           */
     int outer;               /* defect-correction cycles (1 in FP64 mode)                    */
     int status;              /* status of the last solve                                    */
-    int graph_launches;      /* replays of the captured iteration graph                     */
+    int graph_launches;      /* replays of the captured iteration graph (on chip: launches of
+                                up to 2048 iterations)                                      */
     double relres;           /* recursive ||r||/||b|| at exit (FP64 mode)                   */
     double relres_true;      /* ||b - A Phi||/||b||, recomputed in FP64 at exit             */
     double solve_ms;         /* wall time of the last solve call on the device             */
@@ -132,9 +133,13 @@ typedef struct pot3d_stats {
                                 cells; 102/104/108 = wavefront tile of 2/4/8 rows x 128   */
     int chunk_p, chunk_r;    /* radial layers per workgroup chunk, per pass                 */
     int blocks_p, blocks_r;  /* workgroups per launch, per pass                              */
-    int iteration;           /* POT3D_ITER_* of the iterations (FP32 inner ones if refined) */
-    int sweep_rows;          /* one-sweep kernel: tile box rows per wavefront (4, 6 or 8)   */
-    int chunk_s, blocks_s;   /* one-sweep kernel: radial layers per chunk, workgroups      */
+    int iteration;           /* POT3D_ITER_* of the iterations (FP32 inner ones if refined;
+                                POT3D_ITER_TWO_PASS with the phi-line preconditioner, whose
+                                iteration takes two kernels)                               */
+    int sweep_rows;          /* one-sweep kernel: tile box rows per wavefront (4, 6 or 8); 0
+                                if the last solve ran on chip                              */
+    int chunk_s, blocks_s;   /* one-sweep kernel: radial layers per chunk, workgroups; on
+                                chip: layers of a workgroup's box, workgroups              */
     int precond;             /* POT3D_PC_* of the last solve                               */
     int blocks_l;            /* workgroups of the pass z = M^-1 r at a solve's start (0 unless
                                 POT3D_PC_PHI_LINE)                                         */

@@ -443,9 +443,9 @@ void fill_shape(const pot3d_ctx *c, pot3d_stats &st)
     st.blocks_p = c->grid_p.nblocks;
     st.blocks_r = c->grid_r.nblocks;
     st.iteration = one_sweep(c) ? POT3D_ITER_ONE_SWEEP : POT3D_ITER_TWO_PASS;
-    st.sweep_rows = c->sweep_rows;
-    st.chunk_s = c->grid_s.ci;
-    st.blocks_s = c->grid_s.nblocks;
+    st.sweep_rows = c->on_chip ? 0 : c->sweep_rows;
+    st.chunk_s = c->on_chip ? c->oc.m : c->grid_s.ci;
+    st.blocks_s = c->on_chip ? c->oc.nti * c->oc.ntj * c->oc.ntk : c->grid_s.nblocks;
     st.precond = c->precond;
     st.blocks_l = c->precond == POT3D_PC_PHI_LINE ? c->line_blocks : 0;
     if (c->precond == POT3D_PC_PHI_LINE) st.iteration = POT3D_ITER_TWO_PASS;
@@ -755,7 +755,7 @@ int run_fp64(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream_t 
 {
     const bool line = c->precond == POT3D_PC_PHI_LINE;
     const bool sweep = !line && one_sweep(c);
-    const bool chip = sweep && c->oc.m > 0 && onchip_open(c->device);
+    const bool chip = c->on_chip = sweep && c->oc.m > 0 && onchip_open(c->device);
     int rc = start_fp64(c, s, tol, maxit, sweep && !chip);
     if (rc != POT3D_OK) return rc;
     HIP_TRY(c, hipEventRecord(c->ev_loop0, s));
@@ -880,7 +880,7 @@ int run_refined(pot3d_ctx *c, double *phi_out, hipMemcpyKind kind_out, hipStream
     double scale_prev = 0.0;
     const bool line = c->precond == POT3D_PC_PHI_LINE;
     const bool sweep = !line && one_sweep(c);
-    const bool chip = sweep && c->oc.m > 0 && onchip_open(c->device);   // of all segments: one continues another
+    const bool chip = c->on_chip = sweep && c->oc.m > 0 && onchip_open(c->device);   // of all segments: one continues another
     for (;;) {
         int rc = refined_outer_check(c, s, &out);
         if (rc != POT3D_OK) return rc;
@@ -1196,6 +1196,7 @@ void shape_context(pot3d_ctx *c, int nr, int nt, int np, int precision, int devi
                                                                                 : POT3D_ITER_ONE_SWEEP;
     choose_launch(c);
     c->oc = plan_onchip(c);
+    c->on_chip = c->oc.m > 0;
 }
 
 int create_context(const double *r_faces, int nr, const double *t_faces, int nt, const double *p_faces, int np,

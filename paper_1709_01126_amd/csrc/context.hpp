@@ -77,6 +77,7 @@ struct pot3d_ctx {
 
     // One-sweep point-Jacobi iterations of a small grid run on chip
     pot3d::OnchipPlan oc;
+    bool on_chip = false;         // whether the last solve did (before the first: whether it will)
 
     // Preconditioner of single solves (the FP64 iterations, or the FP32 inner
     // ones of the refined mode): point Jacobi (PC1) or the phi-line blocks,
