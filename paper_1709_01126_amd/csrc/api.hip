@@ -48,7 +48,6 @@ int fail(pot3d_ctx *ctx, int code, const std::string &msg)
     return code;
 }
 
-constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 int env_int(const char *name, int dflt)
 {
@@ -1280,7 +1279,7 @@ int create_context(const double *r_faces, int nr, const double *t_faces, int nt,
         onchip_place(c->oc, nr, nt, block);
         layers.resize((size_t)nr + kOnchipMaxLayers);
         polar.resize((size_t)nt);
-        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, layers.data(), polar.data());
+        onchip_tables(c->oc, nr, nt, np, r_faces, t_faces, c->ih_h.data(), upper_bc, layers.data(), polar.data());
         CREATE_TRY(launch_fill<double>(reinterpret_cast<double *>(c->oc.words), (long long)kOnchipWords, 0.0, c->stream));
         CREATE_TRY(hipMemcpyAsync(c->oc.layers, layers.data(), layers.size() * sizeof(OnchipLayer), hipMemcpyHostToDevice, c->stream));
         CREATE_TRY(hipMemcpyAsync(c->oc.polar, polar.data(), polar.size() * sizeof(OnchipRow), hipMemcpyHostToDevice, c->stream));

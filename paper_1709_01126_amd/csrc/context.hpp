@@ -100,6 +100,8 @@ struct pot3d_ctx {
 namespace pot3d {
 namespace host {
 
+constexpr double kTwoPi = 6.283185307179586476925286766559;
+
 // Record msg as the context's (or, for ctx = NULL, the thread's) last error.
 int fail(pot3d_ctx *ctx, int code, const std::string &msg);
 // Integer environment variable, or dflt if unset or not a number.

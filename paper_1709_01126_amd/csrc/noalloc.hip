@@ -241,7 +241,7 @@ extern "C" int pot3d_solve_noalloc(const double *r_faces, int nr, const double *
         shape.sc = sc;
         shape.h_sc = &h_sc;
         onchip_place(shape.oc, nr, nt, base + o_chip);
-        onchip_tables(nr, nt, r_faces, t_faces, upper_bc, h_layers, h_polar);
+        onchip_tables(shape.oc, nr, nt, np, r_faces, t_faces, h_ih, upper_bc, h_layers, h_polar);
         NA_TRY(hipMemcpyAsync(shape.oc.layers, h_layers, ((size_t)nr + kOnchipMaxLayers) * sizeof(OnchipLayer), hipMemcpyHostToDevice, s));
         NA_TRY(hipMemcpyAsync(shape.oc.polar, h_polar, (size_t)nt * sizeof(OnchipRow), hipMemcpyHostToDevice, s));
         NA_TRY(launch_fill<double>(reinterpret_cast<double *>(shape.oc.words), (long long)kOnchipWords, 0.0, s));

@@ -52,6 +52,16 @@
 // trip), and sums posted before the stores have completed with a flag for the
 // neighbours after them (1 to 2 us).
 //
+// The closed wall (CLOSED).  The constants are in A's null space there.  b has
+// none of their part, but rounding puts some eps |r_0| of it into the residual,
+// where no direction reaches it.  Once the rest of the residual is smaller, r.z
+// no longer falls, while p.w does, and alpha and p grow without bound: 1.3
+// times the iterations to 1e-13 further on, Phi was lost.  (The sweeps'
+// operator, a diagonal times p less the neighbours, leaves rounding errors of a
+// constant p in p.w, which end that at a residual of 1e-12 to 1e-6.)  So a
+// sixth sum, of r, gives the constant that z_j holds, and z_{j+1} is formed
+// without it: 45 x 91 x 179 7.92 us per step with it, 7.54 without.
+//
 // All workgroups of a launch must be on the chip at once.  There are at most
 // as many as compute units and each fits one, and the host runs one such
 // launch at a time per device; should they still not come together (another
@@ -78,7 +88,7 @@ namespace {
 
 constexpr int kOcWaves = 8;                   // polar rows of a box
 constexpr int kOcThreads = kOcWaves * kWave;
-constexpr int kOcSums = 5;
+constexpr int kOcSums = 5;      // and a sixth with the closed wall
 static_assert(kOnchipStop == kWave, "a lane looks at its own word");
 
 // Relaxed agent-scope accesses of the exchange.
@@ -103,12 +113,12 @@ __device__ __forceinline__ double wave_sum(double v)
     return (lane_value(v, 15) + lane_value(v, 31)) + (lane_value(v, 47) + lane_value(v, 63));
 }
 
-template <int M, typename V>
+template <int M, typename V, int SUMS>
 struct OcLds {
     V p[M][kOcWaves + 2][kWave + 2];          // p_j of the box and its ring
     V edge[kOcWaves][2 * M];                  // v of the box's left and right cells
-    double acc[kOcSums][kOcThreads];          // per-thread sums
-    double tot[kOcSums];                      // sums over the grid
+    double acc[SUMS][kOcThreads];             // per-thread sums
+    double tot[SUMS];                         // sums over the grid
     double alpha, beta, rho, sigma;           // of this step, for the next
     double rr, relres;
     int k, status, converged, curved, gave_up;
@@ -147,11 +157,12 @@ __device__ __forceinline__ void next_scalars(L &l, int lane)
 }
 
 // Up to `chunk` steps.  seq0: the number before this launch's first step.
-template <int M, typename V>
+template <int M, typename V, bool CLOSED>
 __global__ void __launch_bounds__(kOcThreads)
 onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wait_ticks)
 {
-    __shared__ OcLds<M, V> lds;
+    constexpr int kSums = CLOSED ? kOcSums + 1 : kOcSums;
+    __shared__ OcLds<M, V, kSums> lds;
     constexpr int NJ = (2 * M + kOcWaves - 1) / kOcWaves;   // polar ring rows per wavefront
     static_assert(2 * M * kOcWaves <= kOcThreads, "azimuthal ring: one cell per thread");
     const CPtr<const DevScalars> csc = to_const(a.sc);
@@ -272,6 +283,8 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
     // scalars of the recurrence, uniform (committed once a step is known not to end the solve)
     double s_alpha = csc->alpha, s_beta = csc->beta, s_rho = csc->rho, s_sigma = csc->sigma;
     V alpha = (V)s_alpha, beta = (V)s_beta;
+    V shift = V(0);   // closed wall: the constant that z_j holds (see the top)
+    auto advanced = [&](V zz, V vv, V by) -> V { return vfma<V>(-alpha, vv, CLOSED ? zz - by : zz); };   // z_{j+1}
     const double tol = csc->tol, bnorm = csc->bnorm;
     const int maxit = csc->maxit;
     int sweep = csc->sweep;
@@ -337,7 +350,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
                     const int m = mb + u;
                     const V p0 = kPreg ? p[kPreg ? m : 0] : lp[own_p + m * kLpLayer];
                     xm[u] = vfma<V>(alpha, p0, xm[u]);
-                    z[m] = vfma<V>(-alpha, v[m], z[m]);
+                    z[m] = advanced(z[m], v[m], m < tin ? shift : V(0));   // zeros above the grid
                     const V pn = vfma<V>(beta, p0, z[m]);
                     if constexpr (kPreg) {
                         p[m] = pn;
@@ -350,16 +363,16 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        z_lo = vfma<V>(-alpha, v_lo, z_lo);
+        z_lo = advanced(z_lo, v_lo, shift);
         p_lo = vfma<V>(beta, p_lo, z_lo);
-        z_hi = vfma<V>(-alpha, v_hi, z_hi);
+        z_hi = advanced(z_hi, v_hi, shift);
         p_hi = vfma<V>(beta, p_hi, z_hi);
 #pragma unroll
         for (int n = 0; n < NJ; ++n) {
-            z_j[n] = vfma<V>(-alpha, v_j[n], z_j[n]);
+            z_j[n] = advanced(z_j[n], v_j[n], shift);
             if (j_on(n)) lp[l_j(n)] = vfma<V>(beta, lp[l_j(n)], z_j[n]);
         }
-        z_k = vfma<V>(-alpha, v_k, z_k);
+        z_k = advanced(z_k, v_k, shift);
         if (k_on) lp[l_k] = vfma<V>(beta, lp[l_k], z_k);
         __syncthreads();
 
@@ -368,7 +381,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         // the layers' scalars are read again in every step: held across the
         // steps they would not fit the scalar registers
         asm volatile("" : "+s"(layers), "+v"(lane_off), "+v"(own_p));
-        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0, acc4 = 0.0;
+        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0, acc4 = 0.0, acc5 = 0.0;
         V pim = p_lo, pc = kPreg ? p[0] : lp[own_p];
 #pragma unroll
         for (int m = 0; m < M; ++m) {
@@ -390,6 +403,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
             acc2 = __builtin_fma((double)pc, (double)ap, acc2);
             acc3 = __builtin_fma((double)z[m], (double)ap, acc3);
             acc4 = __builtin_fma((double)v[m], (double)ap, acc4);
+            if constexpr (CLOSED) acc5 += (double)r;
             pim = pc;
             pc = pip;
             if (m & 1) __builtin_amdgcn_sched_barrier(0);   // loads no further ahead: registers
@@ -422,17 +436,18 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         lds.acc[2][tid] = acc2;
         lds.acc[3][tid] = acc3;
         lds.acc[4][tid] = acc4;
+        if constexpr (CLOSED) lds.acc[kSums - 1][tid] = acc5;
         // this wavefront's boundary stores are complete before the workgroup posts
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 
-        if (w < kOcSums) {   // wavefront c posts, awaits and sums component c
+        if (w < kSums) {   // wavefront c posts, awaits and sums component c
             double part = 0.0;
 #pragma unroll
             for (int u = 0; u < kOcWaves; ++u) part += lds.acc[w][u * kWave + lane];
             part = wave_sum(part);
             // records of 16 bytes, two words each: lane pairs store and read them whole
-            unsigned long long *words = a.words + ((seq & 1) * kOcSums + w) * kOnchipSums + kOnchipStop;
+            unsigned long long *words = a.words + ((seq & 1) * kSums + w) * kOnchipSums + kOnchipStop;
             const unsigned long long tag = (unsigned long long)seq << 32;
             if (lane < 2) put_shared(within(kWords, words, 2 * b, lane), tag | (unsigned)(lane ? __double2hiint(part) : __double2loint(part)));
             bool late = false;
@@ -473,7 +488,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         __syncthreads();
         if (lds.gave_up) {   // the same for the whole workgroup
             if (tid == 0) put_shared(&a.sc->gave_up, 1);
-            if (tid < 2 * kOcSums) put_shared(a.words + tid * kOnchipSums, 1ull);
+            if (tid < 2 * kSums) put_shared(a.words + tid * kOnchipSums, 1ull);
             return;
         }
         fetch_ring();   // in flight under the scalars
@@ -490,6 +505,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
                 s_beta = wave_uniform(lds.beta);
                 alpha = (V)s_alpha;
                 beta = (V)s_beta;
+                if constexpr (CLOSED) shift = (V)(wave_uniform(lds.tot[kSums - 1]) * a.inv_dsum);
             } else {
                 stop = true;
                 if (tid == 0) lds.status = POT3D_EBREAKDOWN;
@@ -510,7 +526,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
             if (stop) {
                 *cell(a.p, m) = pm - z[m];
             } else {
-                *cell(a.r, m) = z[m];
+                *cell(a.r, m) = CLOSED ? z[m] - shift : z[m];
                 *cell(a.p, m) = pm;
                 *cell(a.v, m) = v[m];
             }
@@ -535,39 +551,42 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
     }
 }
 
-template <typename V>
-const void *onchip_symbol(int m)
+// The kernel of a plan; NULL: none for these boxes.
+template <typename V, bool CLOSED>
+auto onchip_form(int m) -> void (*)(OnchipArgs<V>, int, unsigned, int, long long)
 {
     switch (m) {
-    case 1: return reinterpret_cast<const void *>(&onchip_kernel<1, V>);
-    case 2: return reinterpret_cast<const void *>(&onchip_kernel<2, V>);
-    case 4: return reinterpret_cast<const void *>(&onchip_kernel<4, V>);
-    case 8: return reinterpret_cast<const void *>(&onchip_kernel<8, V>);
-    case 16: return reinterpret_cast<const void *>(&onchip_kernel<16, V>);
+    case 1: return onchip_kernel<1, V, CLOSED>;
+    case 2: return onchip_kernel<2, V, CLOSED>;
+    case 4: return onchip_kernel<4, V, CLOSED>;
+    case 8: return onchip_kernel<8, V, CLOSED>;
+    case 16: return onchip_kernel<16, V, CLOSED>;
     default: return nullptr;
     }
+}
+template <typename V>
+auto onchip_form(int m, bool closed)
+{
+    return closed ? onchip_form<V, true>(m) : onchip_form<V, false>(m);
 }
 
 }  // namespace
 
 template <typename V>
-hipError_t launch_onchip(const OnchipArgs<V> &a, int m, int chunk, unsigned seq0, int fresh, long long wait_ticks,
-                         hipStream_t s)
+hipError_t launch_onchip(const OnchipArgs<V> &a, int m, bool closed, int chunk, unsigned seq0, int fresh,
+                         long long wait_ticks, hipStream_t s)
 {
     const int nwg = a.nti * a.ntj * a.ntk;
-    if (nwg < 1 || nwg > kOnchipMaxWg || a.ti != m || a.tj > kOcWaves || a.tk > kWave) return hipErrorInvalidValue;
-    switch (m) {
-    case 1: onchip_kernel<1, V><<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks); break;
-    case 2: onchip_kernel<2, V><<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks); break;
-    case 4: onchip_kernel<4, V><<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks); break;
-    case 8: onchip_kernel<8, V><<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks); break;
-    case 16: onchip_kernel<16, V><<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks); break;
-    default: return hipErrorInvalidValue;
-    }
+    const auto kernel = onchip_form<V>(m, closed);
+    if (!kernel || nwg < 1 || nwg > kOnchipMaxWg || a.ti != m || a.tj > kOcWaves || a.tk > kWave)
+        return hipErrorInvalidValue;
+    kernel<<<nwg, kOcThreads, 0, s>>>(a, chunk, seq0, fresh, wait_ticks);
     return hipGetLastError();
 }
-template hipError_t launch_onchip<double>(const OnchipArgs<double> &, int, int, unsigned, int, long long, hipStream_t);
-template hipError_t launch_onchip<float>(const OnchipArgs<float> &, int, int, unsigned, int, long long, hipStream_t);
+template hipError_t launch_onchip<double>(const OnchipArgs<double> &, int, bool, int, unsigned, int, long long,
+                                          hipStream_t);
+template hipError_t launch_onchip<float>(const OnchipArgs<float> &, int, bool, int, unsigned, int, long long,
+                                         hipStream_t);
 
 unsigned onchip_oob_line() { return read_oob_line(); }
 
@@ -587,6 +606,7 @@ OnchipPlan plan_onchip(const pot3d_ctx *c)
     for (const char *name : {"POT3D_SWEEP_ROWS", "POT3D_SWEEP_TJ", "POT3D_SWEEP_TK", "POT3D_SWEEP_CI", "POT3D_SWEEP_X",
                              "POT3D_TARGET_BLOCKS_S", "POT3D_REVERSE_S"})
         if (std::getenv(name)) return o;
+    o.closed = c->upper_bc == POT3D_UPPER_CLOSED_WALL;
     const int slots = std::min(kOnchipMaxWg, c->num_cu);
     o.ntj = (c->nt + kOcWaves - 1) / kOcWaves;
     o.ntk = (c->np + kWave - 1) / kWave;
@@ -600,7 +620,8 @@ OnchipPlan plan_onchip(const pot3d_ctx *c)
     o.m = smallest(8, std::min(64, slots));
     if (!o.m) o.m = smallest(kOnchipMaxLayers, slots);
     if (o.m) {
-        const void *f = c->precision == POT3D_FP32_REFINED ? onchip_symbol<float>(o.m) : onchip_symbol<double>(o.m);
+        const void *f = c->precision == POT3D_FP32_REFINED ? reinterpret_cast<const void *>(onchip_form<float>(o.m, o.closed))
+                                                           : reinterpret_cast<const void *>(onchip_form<double>(o.m, o.closed));
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kOcThreads, 0) != hipSuccess || per_cu < 1) o.m = 0;
     }
@@ -641,8 +662,8 @@ void onchip_place(OnchipPlan &o, int nr, int nt, void *base)
     o.faces = b + faces;
 }
 
-void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper_bc, OnchipLayer *layers,
-                   OnchipRow *polar)
+void onchip_tables(OnchipPlan &o, int nr, int nt, int np, const double *rf, const double *tf, const double *ih,
+                   int upper_bc, OnchipLayer *layers, OnchipRow *polar)
 {
     auto mid = [](const double *f, int q) { return 0.5 * (f[q] + f[q + 1]); };
     for (int i = nr; i < nr + kOnchipMaxLayers; ++i) layers[i] = OnchipLayer{0.0, 0.0, 0.0, 1.0};
@@ -660,6 +681,12 @@ void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper
         polar[j].cp = j < nt - 1 ? std::sin(tf[j + 1]) / (mid(tf, j + 1) - mid(tf, j)) : 0.0;
         polar[j].q = dt / sj;
     }
+    // the diagonal summed over the cells, by its factors (the phi widths add up to 2 pi)
+    double width = 0.0, coupling = 0.0, face = 0.0, polar_c = 0.0, azimuthal = 0.0, inverse = 0.0;
+    for (int i = 0; i < nr; ++i) width += layers[i].dr, coupling += layers[i].sum;
+    for (int j = 0; j < nt; ++j) face += polar[j].face, polar_c += polar[j].cm + polar[j].cp, azimuthal += polar[j].q;
+    for (int k = 0; k < np; ++k) inverse += ih[k];
+    o.inv_dsum = 1.0 / (kTwoPi * (face * coupling + width * polar_c) + 2.0 * width * azimuthal * inverse);
 }
 
 std::mutex &onchip_lock(int device)
@@ -694,8 +721,8 @@ static int queue_with(pot3d_ctx *c, V *r, V *x, V *p, V *v, V *faces, DevScalars
 {
     OnchipPlan &o = c->oc;
     OnchipArgs<V> a{c->nr, c->nt, c->np, c->pitch, o.ti, o.tj, o.tk, o.nti, o.ntj, o.ntk, o.layers, o.polar,
-                    c->dphi, c->ih, r, x, p, v, faces, sc, o.words, c->npad};
-    HIP_TRY(c, launch_onchip<V>(a, o.m, chunk, o.seq, fresh ? 1 : 0, o.wait_ticks, s));
+                    c->dphi, c->ih, r, x, p, v, faces, sc, o.words, c->npad, o.inv_dsum};
+    HIP_TRY(c, launch_onchip<V>(a, o.m, o.closed, chunk, o.seq, fresh ? 1 : 0, o.wait_ticks, s));
     o.seq += (unsigned)chunk;
     return POT3D_OK;
 }

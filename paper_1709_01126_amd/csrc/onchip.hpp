@@ -30,9 +30,11 @@ struct OnchipPlan {
     int m = 0;
     int ti = 0, tj = 0, tk = 0, nti = 0, ntj = 0, ntk = 0;
     unsigned seq = 0;                 // number of the last exchange step
+    bool closed = false;              // closed upper wall: A has the constants in its null space
+    double inv_dsum = 0.0;            // 1 / the sum of A's diagonal (onchip_tables)
     long long wait_ticks = 0;         // longest wait of an exchange (device wall clock)
     double retry_s = 0.0;             // how long the device stays with sweeps after a give-up
-    unsigned long long *words = nullptr;   // device: posted sums, [2][5][kOnchipSums]
+    unsigned long long *words = nullptr;   // device: posted sums, [2][6][kOnchipSums]
     void *faces = nullptr;                 // device: the workgroups' boundary cells (FP64, or FP32 in refined contexts)
     size_t face_bytes = 0;
     size_t bytes = 0;                      // of the four arrays together (onchip_place)
@@ -45,7 +47,7 @@ constexpr int onchip_faces(int m) { return 2 * (8 * 64 + m * 64 + m * 8) + 16; }
 // once an exchange has waited too long, then two words per workgroup.
 constexpr int kOnchipStop = 64;
 constexpr int kOnchipSums = kOnchipStop + 2 * kOnchipMaxWg;
-constexpr size_t kOnchipWords = 2 * 5 * (size_t)kOnchipSums;
+constexpr size_t kOnchipWords = 2 * 6 * (size_t)kOnchipSums;
 
 template <typename V>
 struct OnchipArgs {
@@ -62,22 +64,24 @@ struct OnchipArgs {
     DevScalars *sc;
     unsigned long long *words;
     long long npad;
+    double inv_dsum;   // closed wall: OnchipPlan's
 };
 
 // One launch of up to `chunk` iterations.  seq0: plan.seq; fresh: no launch of
 // this solve has run yet.
 template <typename V>
-hipError_t launch_onchip(const OnchipArgs<V> &a, int m, int chunk, unsigned seq0, int fresh, long long wait_ticks,
-                         hipStream_t s);
+hipError_t launch_onchip(const OnchipArgs<V> &a, int m, bool closed, int chunk, unsigned seq0, int fresh,
+                         long long wait_ticks, hipStream_t s);
 unsigned onchip_oob_line();   // take_oob's line of onchip.hip, 0 if none
 
 namespace host {
 
 // The plan for a context's grid and precision (m = 0 if it does not fit).
 OnchipPlan plan_onchip(const pot3d_ctx *c);
-// Host tables of the operator's factors (nr + kOnchipMaxLayers layers, nt polar rows).
-void onchip_tables(int nr, int nt, const double *rf, const double *tf, int upper_bc, OnchipLayer *layers,
-                   OnchipRow *polar);
+// Host tables of the operator's factors (nr + kOnchipMaxLayers layers, nt polar
+// rows), and from them and 1/(phi differences) ih the plan's inv_dsum.
+void onchip_tables(OnchipPlan &o, int nr, int nt, int np, const double *rf, const double *tf, const double *ih,
+                   int upper_bc, OnchipLayer *layers, OnchipRow *polar);
 // The plan's arrays in `bytes` of device memory at base, words first.
 void onchip_place(OnchipPlan &o, int nr, int nt, void *base);
 // Resident launches of one device run one at a time: held from before a launch
