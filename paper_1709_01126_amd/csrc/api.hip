@@ -1184,9 +1184,12 @@ void shape_context(pot3d_ctx *c, int nr, int nt, int np, int precision, int devi
     c->graph_m = std::max(2, env_int("POT3D_GRAPH_ITERS", 16));
     c->graph_m += c->graph_m & 1;   // even, so the p buffers alternate consistently across replays
     // Default form: one sweep, except for the FP32 inner iterations of grids
-    // whose vectors stream from HBM, where the two FP32 passes in their
-    // streaming shape are faster (301 x 641 x 1281: 2.08 against 2.35 ms per
-    // inner iteration; 151 x 301 x 601: 201 against 197 us).
+    // whose vectors stream from HBM, which run in two FP32 passes in their
+    // streaming shape.  The line was drawn when a sweep read and wrote r and p
+    // (301 x 641 x 1281: 2.35 ms per inner iteration against 2.08 in two passes);
+    // the sweeps of the last two directions are the faster form there too (1.48
+    // against 1.95 ms; 240 x 520 x 1040 0.62 against 0.93; 151 x 301 x 601 146
+    // against 194 us), and pot3d_set_iteration selects them.
     const int it_env = env_int("POT3D_ITERATION", -1);
     if (it_env == POT3D_ITER_TWO_PASS || it_env == POT3D_ITER_ONE_SWEEP)
         c->iteration = it_env;
