@@ -75,7 +75,9 @@ KERNEL_KEYS = {"sweep_even": (24.0, ("stencil_sweep<", "double, 1>")),
                "line": (16.0, ("line_solve_kernel<",)),
                # the phi-line iteration: step (the mean of 24 N and, with x, 40 N) and curvature
                "line_step": (32.0, ("line_iteration_kernel<", "double, true>")),
-               "line_curvature": (8.0, ("line_iteration_kernel<", "double, false>"))}
+               "line_curvature": (8.0, ("line_iteration_kernel<", "double, false>")),
+               # by themselves on packed rows: the operator, and the field (the wall layers beside 32 N left out)
+               "apply": (16.0, ("stencil_march<", ", 0, double>")), "field": (32.0, ("field_kernel",))}
 
 
 def moved_bytes(stats, n: int) -> float:
@@ -552,6 +554,9 @@ def main():
     if args.profile_kernels:
         # both iteration forms: the one-sweep kernel, then the two passes
         solver.solve_device(d_br, d_phi, 0.0, 8)
+        for _ in range(4):
+            solver.field()
+            solver.apply(d_phi, torch.empty_like(d_phi))
         ms_se, ms_so = solver.time_kernels(args.kernel_reps)
         solver.set_iteration(pot3d.ITER_TWO_PASS)
         solver.solve_device(d_br, d_phi, 0.0, 8)
