@@ -60,7 +60,7 @@
 // operator, a diagonal times p less the neighbours, leaves rounding errors of a
 // constant p in p.w, which end that at a residual of 1e-12 to 1e-6.)  So a
 // sixth sum, of r, gives the constant that z_j holds, and z_{j+1} is formed
-// without it: 45 x 91 x 179 7.92 us per step with it, 7.54 without.
+// without it: 45 x 91 x 179 7.8 us per step with it, 7.3 without.
 //
 // All workgroups of a launch must be on the chip at once.  There are at most
 // as many as compute units and each fits one, and the host runs one such
@@ -595,9 +595,9 @@ namespace host {
 // Boxes of the fewest layers, up to 8, that take at most 64 workgroups;
 // otherwise of the fewest that take at most one per compute unit.  A step is
 // one lane's chain of layers plus an exchange that grows with the workgroups:
-// 32 x 64 x 128 took 5.7 us per step with 64 workgroups of 8 layers, 5.9 with
-// 128 of 4, 6.4 with 256 of 2 and 8.9 with 32 of 16; 45 x 91 x 179 7.6 with 216
-// of 8 and 10.2 with 108 of 16.  (Its sweeps take 32 and 42 us.)
+// 32 x 64 x 128 took 5.5 us per step with 64 workgroups of 8 layers, 5.6 with
+// 128 of 4, 6.0 with 256 of 2 and 9.0 with 32 of 16; 45 x 91 x 179 7.3 with 216
+// of 8 and 10.3 with 108 of 16.  (Its sweeps take 32 and 42 us.)
 OnchipPlan plan_onchip(const pot3d_ctx *c)
 {
     OnchipPlan o;
