@@ -60,7 +60,7 @@
 // operator, a diagonal times p less the neighbours, leaves rounding errors of a
 // constant p in p.w, which end that at a residual of 1e-12 to 1e-6.)  So a
 // sixth sum, of r, gives the constant that z_j holds, and z_{j+1} is formed
-// without it: 45 x 91 x 179 7.8 us per step with it, 7.3 without.
+// without it: 45 x 91 x 179 7.4 us per step with it, 7.2 without.
 //
 // All workgroups of a launch must be on the chip at once.  There are at most
 // as many as compute units and each fits one, and the host runs one such
@@ -320,6 +320,11 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
 #endif
     };
     constexpr int kFaces = onchip_faces(M), kWords = 2 * kOnchipMaxWg;
+    // The stop words lie behind the sums, which so need one address less per lane
+    // (10 x 20 x 40 3.34 us per step against 3.64, 45 x 91 x 179 7.1 against 7.2
+    // and with the closed wall 7.4 against 7.7); boxes of 16 layers have them in
+    // front (64 x 128 x 256 11.6 us against 11.7, FP32 8.6 against 8.9).
+    constexpr int kFirstStop = M == 16 ? 0 : kWords, kFirstSum = M == 16 ? kOnchipStop : 0;
     const int step_i = a.ntk * a.ntj;
     const int g_k = kside ? (kt + 1 < a.ntk ? b + 1 : b + 1 - a.ntk) : (kt > 0 ? b - 1 : b + a.ntk - 1);
     auto fetch_ring = [&]() {
@@ -447,7 +452,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
             for (int u = 0; u < kOcWaves; ++u) part += lds.acc[w][u * kWave + lane];
             part = wave_sum(part);
             // records of 16 bytes, two words each: lane pairs store and read them whole
-            unsigned long long *words = a.words + ((seq & 1) * kSums + w) * kOnchipSums + kOnchipStop;
+            unsigned long long *words = a.words + ((seq & 1) * kSums + w) * kOnchipSums + kFirstSum;
             const unsigned long long tag = (unsigned long long)seq << 32;
             if (lane < 2) put_shared(within(kWords, words, 2 * b, lane), tag | (unsigned)(lane ? __double2hiint(part) : __double2loint(part)));
             bool late = false;
@@ -466,7 +471,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
                     for (int u = 0; u < NW; ++u) ok = ok && (unsigned)(got[u] >> 32) == seq;
                     if (__all(ok)) break;
                     if ((n & 15) == 0 || wait_ticks == 0) {   // bounded: see the top
-                        const bool stopped = __any(get_shared(words - kOnchipStop + lane) != 0);
+                        const bool stopped = __any(get_shared(words + (kFirstStop - kFirstSum) + lane) != 0);
                         late = stopped | (wall_clock64() - t0 >= wait_ticks);
                     }
                     if (late) break;
@@ -488,7 +493,7 @@ onchip_kernel(OnchipArgs<V> a, int chunk, unsigned seq0, int fresh, long long wa
         __syncthreads();
         if (lds.gave_up) {   // the same for the whole workgroup
             if (tid == 0) put_shared(&a.sc->gave_up, 1);
-            if (tid < 2 * kSums) put_shared(a.words + tid * kOnchipSums, 1ull);
+            if (tid < 2 * kSums) put_shared(a.words + tid * kOnchipSums + kFirstStop, 1ull);
             return;
         }
         fetch_ring();   // in flight under the scalars
@@ -595,9 +600,10 @@ namespace host {
 // Boxes of the fewest layers, up to 8, that take at most 64 workgroups;
 // otherwise of the fewest that take at most one per compute unit.  A step is
 // one lane's chain of layers plus an exchange that grows with the workgroups:
-// 32 x 64 x 128 took 5.5 us per step with 64 workgroups of 8 layers, 5.6 with
-// 128 of 4, 6.0 with 256 of 2 and 9.0 with 32 of 16; 45 x 91 x 179 7.3 with 216
-// of 8 and 10.3 with 108 of 16.  (Its sweeps take 32 and 42 us.)
+// 32 x 64 x 128 took 5.4 us per step with 64 workgroups of 8 layers or 128 of 4,
+// 6.0 with 256 of 2 and 9.0 with 32 of 16; 16 x 60 x 120 4.7 with 64 of 4, 5.0
+// with 32 of 8 and 5.1 with 128 of 2; 45 x 91 x 179 7.2 with 216 of 8 and 10.2
+// with 108 of 16.  (Its sweeps take 32 and 42 us.)
 OnchipPlan plan_onchip(const pot3d_ctx *c)
 {
     OnchipPlan o;

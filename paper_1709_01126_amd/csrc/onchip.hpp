@@ -43,8 +43,8 @@ struct OnchipPlan {
 };
 // Boundary cells of a box of m layers, with some cells between the boxes' sets.
 constexpr int onchip_faces(int m) { return 2 * (8 * 64 + m * 64 + m * 8) + 16; }
-// Posted sums of one step and component: kOnchipStop words of which any is set
-// once an exchange has waited too long, then two words per workgroup.
+// Posted sums of one step and component: two words per workgroup, and beside
+// them kOnchipStop words of which any is set once an exchange has waited too long.
 constexpr int kOnchipStop = 64;
 constexpr int kOnchipSums = kOnchipStop + 2 * kOnchipMaxWg;
 constexpr size_t kOnchipWords = 2 * 6 * (size_t)kOnchipSums;

@@ -143,7 +143,7 @@ struct pot3d_server {
     DevScalars *h_status = nullptr;   // pinned, [3][slot]: statuses after the two latest replays, and of the on-chip slots
     Replay replay[2];
     int last = -1;                    // replay buffer of the most recent launch
-    hipEvent_t chip_done[2] = {nullptr, nullptr};   // the two latest launches of on-chip slots
+    hipEvent_t chip_first = nullptr, chip_last = nullptr;   // a step's on-chip launches
     std::vector<BatchGraph> graphs;   // captured batched graphs by launch widths
     unsigned long long graph_clock = 0;
     int need_p = 0, need_r = 0;   // workgroups the active slots own in each pass (need_p: the sweep)
@@ -563,7 +563,7 @@ int pot3d_server_create(int device, int precision, int max_slots, double hbm_bud
     hipError_t e = hipStreamCreateWithFlags(&p->stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking);
     for (int b = 0; b < 2 && e == hipSuccess; ++b) {
-        e = hipEventCreateWithFlags(&p->chip_done[b], hipEventDisableTiming);
+        e = hipEventCreateWithFlags(b ? &p->chip_last : &p->chip_first, hipEventDisableTiming);
         if (e != hipSuccess) break;
         p->replay[b].req.assign(max_slots, nullptr);
         p->replay[b].phase.assign(max_slots, 0);
@@ -646,8 +646,8 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         const int rc = graph_for(sv, sv->need_p, sv->need_r, &g);
         if (rc != POT3D_OK) return rc;
     }
-    // 1. small grids advance on chip, one after the other.  One launch runs while
-    //    the one before is looked at: if that has given up, the slots behind it
+    // 1. small grids advance on chip, one after the other.  The first launch is
+    //    looked at while the second runs: if it has given up, the slots behind
     //    don't wait for the same reason in turn.
     DevScalars *const chip_status = sv->h_status + 2 * sv->max_slots;
     bool gave_up = false;
@@ -664,14 +664,14 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
             sl.launches += 1;
             SV_TRY(sv, hipMemcpyAsync(&chip_status[q], sv->precision == POT3D_FP64 ? sl.ctx->sc : sl.ctx->sc32,
                                       sizeof(DevScalars), hipMemcpyDeviceToHost, s));
-            const size_t n = ran.size();
-            SV_TRY(sv, hipEventRecord(sv->chip_done[n & 1], s));
-            if (n > 0) {
-                SV_TRY(sv, hipEventSynchronize(sv->chip_done[(n - 1) & 1]));
-                gave_up = chip_status[ran.back()].gave_up != 0;
-            }
             ran.push_back(q);
+            if (ran.size() == 1 && chips > 1) SV_TRY(sv, hipEventRecord(sv->chip_first, s));
+            if (ran.size() == 2) {
+                SV_TRY(sv, hipEventSynchronize(sv->chip_first));
+                gave_up = chip_status[ran[0]].gave_up != 0;
+            }
         }
+        if (batched > 0) SV_TRY(sv, hipEventRecord(sv->chip_last, s));
     }
     // 2. queue the next replay of the active slots (the tables are current),
     //    with a copy of each slot's scalars after it
@@ -696,7 +696,7 @@ int pot3d_server_step(pot3d_server *sv, int *n_active, int *n_queued, long long 
         launched = b;
     }
     if (chips > 0) {   // the replay runs on; the resident launches are over
-        SV_TRY(sv, hipEventSynchronize(sv->chip_done[(ran.size() - 1) & 1]));
+        SV_TRY(sv, batched > 0 ? hipEventSynchronize(sv->chip_last) : hipStreamSynchronize(s));
         resident.unlock();
         ++sv->replays;
         for (int q : ran) gave_up = gave_up || chip_status[q].gave_up != 0;
@@ -899,7 +899,7 @@ void pot3d_server_destroy(pot3d_server *sv)
                     sv->d_r32[0], sv->d_r32[1], sv->d_s64, sv->d_s32, sv->d_finp, sv->d_finr};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
-    for (hipEvent_t ev : sv->chip_done)
+    for (hipEvent_t ev : {sv->chip_first, sv->chip_last})
         if (ev) (void)hipEventDestroy(ev);
     if (sv->h_status) (void)hipHostFree(sv->h_status);
     for (Replay &r : sv->replay)
