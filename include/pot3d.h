@@ -250,7 +250,8 @@ int pot3d_get_stats(const pot3d_ctx *ctx, pot3d_stats *out);
  * the r/x update (r.z, r.r).  One-sweep iteration: *ms_update_p = the even
  * sweeps (x left to the next sweep), *ms_update_r = the odd sweeps (x of the
  * pair); with POT3D_SWEEP_X=1 both time the sweep that updates x every time.
- * FP32-refined contexts time the FP32 inner kernels.  It runs on the vectors
+ * FP32-refined contexts time the FP32 inner kernels.  Contexts whose solves run
+ * on chip time the sweeps, which those solves don't use.  It runs on the vectors
  * the context holds and overwrites them; a later solve re-initializes
  * everything.
  */

@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-HOLD_MS = 1500
+HOLD_MS = 4000
 
 
 def test_device_stays_with_sweeps_for_a_while(monkeypatch):
